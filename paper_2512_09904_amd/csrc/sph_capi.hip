@@ -178,6 +178,11 @@ static size_t carve(const Plan& P, void* base, SlotDesc* d) {
   C.take(D.nsc, nf * 4);
   C.take(D.nrec, 4 * (size_t)P.rowlen_f);
   C.take(D.srec, 4 * (size_t)P.rowlen_s);
+  if (P.prec != SPH_PREC_FP64) {   // what the staged sweeps read
+    C.take(D.bhead, nbf * sizeof(BlkHead));
+    C.take(D.blist, nbf * STAGE_CAP * 4);
+    C.takev(D.vdb, 4 * ns * rs);
+  }
   C.take(D.rmaj, 4 * nf * (size_t)(P.kf + P.ks));
   C.takev(D.xo, 4 * nf * rs);
   C.takev(D.so, 4 * ns * rs);
@@ -201,6 +206,7 @@ static size_t carve(const Plan& P, void* base, SlotDesc* d) {
   C.take(D.sperm, ns * 4);
   C.take(D.zeta, ns * 8);
   C.takev(D.vd, 4 * ns * rs);
+  C.takev(D.nuw, 4 * ns * rs);
   C.take(D.skey, ns * 8);
   C.take(D.rank, nc * 4);
   C.take(D.cnt_f, nc * 4);
@@ -1405,6 +1411,23 @@ extern "C" int sph_debug_dump(sph_solver* s, int32_t what, void* buf, size_t byt
       LCHK(d2h(r.data(), sol ? D.srec : D.nrec, r.size() * 4));
       uint32_t* o = (uint32_t*)buf;
       unsell(pl, K, [&](size_t i, int k, size_t src) { o[i * (size_t)K + (size_t)k] = r[src]; });
+      if (pl.prec == SPH_PREC_FP64) return SPH_OK;
+      // blocks with staged candidates hold local indices, [slice][k / 4][lane]
+      // in groups of four entries; back to sorted indices by the block's list
+      const size_t nb = (size_t)pl.nblk[DOM_FLUID];
+      std::vector<BlkHead> hd(nb);
+      std::vector<uint32_t> list(nb * STAGE_CAP), cnt(nf);
+      LCHK(d2h(hd.data(), D.bhead, nb * sizeof(BlkHead)));
+      LCHK(d2h(list.data(), D.blist, list.size() * 4));
+      LCHK(d2h(cnt.data(), sol ? D.nsc : D.nfc, nf * 4));
+      for (size_t i = 0; i < nf; ++i) {
+        if (hd[i / BLOCK].n < 0) continue;
+        const uint32_t* row = r.data() + (i / WAVE) * (size_t)K * WAVE;
+        const uint32_t* glob = list.data() + (i / BLOCK) * STAGE_CAP;
+        for (size_t k = 0; k < (size_t)K; ++k)
+          o[i * (size_t)K + k] =
+              k < cnt[i] ? glob[(row[((k / 4) * WAVE + i % WAVE) * 4 + k % 4] & 0xffffu) / 16] : 0u;
+      }
       return SPH_OK;
     }
     case SPH_DUMP_FLUID_OFFSET:

@@ -30,6 +30,29 @@ struct LaunchTab {
   int32_t blk0[NDOM][MAX_SLOTS + 1];
 };
 
+// Neighbour candidates of one fluid block (BLOCK consecutive sorted
+// particles): the fluid, then the solid particles of the cells in the 27-cell
+// stencils of the block's particles, each cell once, numbered 0..n-1 ("local
+// index", the solids from a multiple of 64 on).  With n >= 0 the FP32 sweeps
+// stage the candidates' records in LDS and the block's rows hold
+//   16 * (local index) | 4 * (stencil cell 0..26) << 16
+// in groups of four; with n < 0 the rows hold sorted indices and the sweeps
+// gather from memory.  FP64 mode has neither heads nor lists: its rows always
+// hold sorted indices.
+constexpr int STAGE_CAP = 2432;      // 32 B per candidate: two blocks' worth fit the CU's 160 KB
+struct BlkHead {
+  int32_t n;
+  int32_t ns0;                       // local index of the first solid particle
+  int32_t pad[2];
+};
+constexpr int STAGE_ITEMS = 256;     // cells per block and set (at most 255 used)
+// One cell of a block's candidates: sorted particles [start, start + cnt) have
+// the local indices base.. in the same order.
+struct alignas(8) BlkItem {
+  uint32_t start;
+  uint16_t base, cnt;
+};
+
 // Device-resident control block of a slot, written only by kernels.
 struct SlotCtl {
   double t, dt_ad, dt;
@@ -56,7 +79,8 @@ struct SlotCtl {
 //   cell-relative position (ox, oy, oz, packed cell coordinates), frozen at
 //   the build: x = lo + c cs_r + o, so r_ij = (o_i - o_j) + (c_i - c_j) cs_r
 //   with c_i - c_j in {-1, 0, 1} per axis for every pair
-// A neighbour row entry is the neighbour's sorted index (4 B).
+// A neighbour row entry (4 B) names the neighbour among the block's candidates
+// (BlkHead) or by its sorted index.
 struct SlotDesc {
   int32_t nf, ns, ncells, nslices;
   int32_t kf, ks, nbody, nac_bound;
@@ -90,6 +114,8 @@ struct SlotDesc {
   // the cell-relative positions the sweeps take r_ij from
   uint32_t *nfc, *nsc;
   uint32_t *nrec, *srec;
+  BlkHead *bhead;       // per fluid block
+  uint32_t *blist;      // [fluid block][STAGE_CAP]: the candidates' sorted indices
   uint32_t *rmaj;       // build output: per particle kf fluid then ks solid entries
   void *xo, *so;
   // solids: FP64 reference pose (x, y, z, 0) and normal, body; current pose
@@ -103,6 +129,8 @@ struct SlotDesc {
   void *xwb, *nwb, *vwb, *levb;
   uint32_t *scell, *sperm;
   double *zeta;         // contact factor per solid particle, original order
+  void *nuw;            // wall normal and u_w = -n . v_w per sorted solid particle (FP32 sweeps)
+  void *vdb;            // dummy velocity and body per sorted solid particle (FP32 sweeps)
   void *vd;             // dummy velocity of eq. 18 per sorted solid particle (vx, vy, vz, dp^3 sum W)
   uint64_t *skey;
   // cells

@@ -67,8 +67,8 @@ __device__ __forceinline__ T win_get(const T* lds, const GLB T* g, uint32_t j, c
 }
 
 // per-thread accumulators for up to NACC (= 2) bodies touched by one fluid
-// particle; explicit register arrays, selected by branches (no indexing by a
-// runtime value, so nothing goes to scratch)
+// particle; explicit register arrays (no indexing by a runtime value, so
+// nothing goes to scratch)
 template <int W>
 struct BodyAcc {
   int id0, id1;
@@ -78,34 +78,87 @@ struct BodyAcc {
 #pragma unroll
     for (int k = 0; k < W; ++k) v0[k] = v1[k] = 0.0;
   }
-  // adds x[0..W) to body b; false when both accumulators hold other bodies
-  __device__ __forceinline__ bool add(int b, const double (&x)[W]) {
-    const bool s0 = id0 < 0 || id0 == b;
-    id0 = s0 ? b : id0;
-    const bool s1 = !s0 && (id1 < 0 || id1 == b);
-    id1 = s1 ? b : id1;
+  // Makes b the current body, whose sums are in v0 (a change of body exchanges
+  // the two); false when both accumulators hold other bodies.  Nearly every
+  // particle touches one body, and a wavefront skips the exchange when no lane
+  // needs it.
+  __device__ __forceinline__ bool select(int b) {
+    if (b != id0) {
+      if (id0 >= 0) {
+        const int t = id0;
+        id0 = id1;
+        id1 = t;
 #pragma unroll
-    for (int k = 0; k < W; ++k) {
-      v0[k] += s0 ? x[k] : 0.0;
-      v1[k] += s1 ? x[k] : 0.0;
+        for (int k = 0; k < W; ++k) {
+          const double u = v0[k];
+          v0[k] = v1[k];
+          v1[k] = u;
+        }
+      }
+      if (id0 < 0) id0 = b;
+      if (id0 != b) return false;
     }
-    return s0 || s1;
+    return true;
+  }
+  // Bodies of four staged wall entries: those past the row's end take the
+  // current body.  True when every lane's four are its current body (the first
+  // entry of a row opens it), so that no exchange is needed.
+  __device__ __forceinline__ bool current(const float (&w)[4], const bool (&real)[4], int (&b)[4]) {
+    if (id0 < 0) id0 = (int)w[0];
+    bool odd = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      b[u] = real[u] ? (int)w[u] : id0;
+      odd = odd || b[u] != id0;
+    }
+    return !__any(odd);
+  }
+  // one wall pair's acceleration f and its moment about the body centre (lever
+  // arm l)
+  template <class Real, class Real4>
+  __device__ __forceinline__ void moment(Real fx, Real fy, Real fz, const Real4 l) {
+    const double x = fx, y = fy, z = fz, lx = l.x, ly = l.y, lz = l.z;
+    v0[0] += x;
+    v0[1] += y;
+    v0[2] += z;
+    v0[3] = fma(-lz, y, fma(ly, z, v0[3]));
+    v0[4] = fma(-lx, z, fma(lz, x, v0[4]));
+    v0[5] = fma(-ly, x, fma(lx, y, v0[5]));
+  }
+  // accelerations to forces of the fluid on the body: components [0, 6) times -m
+  __device__ __forceinline__ void to_force(double m) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      v0[k] *= -m;
+      v1[k] *= -m;
+    }
   }
 };
 
 // Deterministic block reduction of per-thread body accumulators: for each
-// body and component, wave butterfly then the four waves in order.
+// body and component, the wavefront by DPP lane moves in a fixed order, then
+// the four waves in order.  A wavefront skips the bodies none of its lanes
+// touches (by LDS permutes over all bodies and components the reduction took
+// about a quarter of the momentum sweep on a tank: 0.41 against 0.30 ms at
+// 1.9 M particles).
 template <int W>
 // out is quantity-major: out[(b * W + k) * nblk + lb]
 __device__ __forceinline__ void block_body_reduce(const BodyAcc<W> acc, int nbody, double* out, size_t nblk,
                                                   int lb, bool accumulate, double* lds /* [4][NB][W] */) {
   const int wv = threadIdx.x / WAVE, ln = threadIdx.x % WAVE;
   for (int b = 0; b < nbody; ++b) {
+    double* o = lds + (wv * NB + b) * W;
+    if (!__any(acc.id0 == b || acc.id1 == b)) {
+      if (ln < W) o[ln] = 0.0;
+      continue;
+    }
+    double s[W];
 #pragma unroll
-    for (int k = 0; k < W; ++k) {
-      const double x = (acc.id0 == b ? acc.v0[k] : 0.0) + (acc.id1 == b ? acc.v1[k] : 0.0);
-      const double s = wave_sum(x);
-      if (ln == 0) lds[(wv * NB + b) * W + k] = s;
+    for (int k = 0; k < W; ++k)
+      s[k] = wave_total((acc.id0 == b ? acc.v0[k] : 0.0) + (acc.id1 == b ? acc.v1[k] : 0.0));
+    if (ln == 0) {
+#pragma unroll
+      for (int k = 0; k < W; ++k) o[k] = s[k];
     }
   }
   __syncthreads();
@@ -449,8 +502,12 @@ __global__ __launch_bounds__(BLOCK) void k_reorder(const SlotDesc* table, Launch
     int c[3];
     cell_coords<typename P::Pos>(S, xp.x, xp.y, xp.z, c);   // in the grid: checked by the pose
     gp<Real4>(S.so)[k] = cell_offset<P>(S, xp.x, xp.y, xp.z, c);
-    gp<Real4>(S.nw)[k] = gpc<Real4>(S.nwb)[s];
-    gp<Real4>(S.vw)[k] = gpc<Real4>(S.vwb)[s];
+    Real4 nq = gpc<Real4>(S.nwb)[s];
+    const Real4 vq = gpc<Real4>(S.vwb)[s];
+    gp<Real4>(S.nw)[k] = nq;
+    gp<Real4>(S.vw)[k] = vq;
+    nq.w = -dot_fma(nq.x, nq.y, nq.z, vq.x, vq.y, vq.z);
+    gp<Real4>(S.nuw)[k] = nq;
     gp<Real4>(S.lev)[k] = gpc<Real4>(S.levb)[s];
     S.body[k] = S.bodyb[s];
     S.sid[k] = S.sidb[s];
@@ -495,17 +552,6 @@ __device__ __forceinline__ double kernel_W_d2(double d2, double inv_h, double kW
   return kW * t * t * t * t * (1.0 + 2.0 * q);
 }
 
-// value of lane l (wave-uniform l) as a scalar
-__device__ __forceinline__ float rl(float v, int l) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
-}
-__device__ __forceinline__ double rl(double v, int l) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
 // Exclusive prefix sum over the wavefront's lanes; *total receives the sum.
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t* total) {
   const int lane = threadIdx.x & (WAVE - 1);
@@ -528,15 +574,17 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // Candidates of one run's stencil against the run's particles [L, R) of the
 // wave.  pre/beg: per stencil cell (27) the prefix of candidate counts and the
-// first index.  Hits of particle p go to row[p] + off, counted in lane p's cnt.
+// first index; lcl (LOCAL): the row entry of its first particle.  Hits of
+// particle p go to its row, counted in lane p's cnt: sorted indices, or (LOCAL)
+// entries of staged rows; own: this lane's particle as such an entry.
 // candidate slots per lane: four keeps the build at five waves per SIMD
 // (92 registers); eight (124 registers, four waves) was 3 % slower
 constexpr int CB = 4;
-template <class Pos, class Pos4>
+template <bool LOCAL, class Pos, class Pos4>
 __device__ __forceinline__ void run_candidates(const GLB Pos4* x, const uint32_t* pre, const uint32_t* beg,
-                                               uint32_t M, int L, int R, int wbase, Pos xi, Pos yi, Pos zi,
-                                               double cut2, GLB uint32_t* rows, int kr, int off, int cap,
-                                               int& cnt, bool self) {
+                                               const uint32_t* lcl, uint32_t M, int L, int R, int wbase, Pos xi,
+                                               Pos yi, Pos zi, double cut2, GLB uint32_t* rows, int kr, int off,
+                                               int cap, int& cnt, uint32_t own) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & (WAVE - 1);
   for (uint32_t b0 = 0; b0 < M; b0 += (uint32_t)(WAVE * CB)) {
@@ -554,7 +602,7 @@ __device__ __forceinline__ void run_candidates(const GLB Pos4* x, const uint32_t
           if (q + st < 27 && pre[q + st] <= m) q += st;
         const uint32_t j = beg[q] + (m - pre[q]);
         const Pos4 pj = x[j];
-        cj[u] = j;
+        cj[u] = LOCAL ? lcl[q] + 16u * (m - pre[q]) : j;
         cx[u] = pj.x;
         cy[u] = pj.y;
         cz[u] = pj.z;
@@ -563,16 +611,16 @@ __device__ __forceinline__ void run_candidates(const GLB Pos4* x, const uint32_t
     const int nu = (int)min((uint32_t)CB, (M - b0 + WAVE - 1) / WAVE);
     for (int p = L; p < R; ++p) {
       const Pos px = rl(xi, p), py = rl(yi, p), pz = rl(zi, p);
-      const uint32_t ip = (uint32_t)(wbase + p);
+      const uint32_t ip = (uint32_t)__builtin_amdgcn_readlane((int)own, p);
       int c = __builtin_amdgcn_readlane(cnt, p);
-      GLB uint32_t* row = rows + (int64_t)ip * kr + off;
+      GLB uint32_t* row = rows + (int64_t)(wbase + p) * kr + off;
 #pragma unroll
       for (int u = 0; u < CB; ++u) {
         if (u >= nu) break;
         const Pos ddx = px - cx[u], ddy = py - cy[u], ddz = pz - cz[u];
         const Pos s2 = ddx * ddx + ddy * ddy;
         const Pos d2 = s2 + ddz * ddz;
-        const bool hit = (double)d2 < cut2 && !(self && cj[u] == ip);
+        const bool hit = (double)d2 < cut2 && cj[u] != ip;
         const uint64_t mask = __ballot(hit);
         if (hit) {
           const int k = c + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
@@ -586,14 +634,107 @@ __device__ __forceinline__ void run_candidates(const GLB Pos4* x, const uint32_t
   }
 }
 
+// The block's candidate cells (BlkHead, BlkItem).  home: the distinct cells of
+// the block's particles in order (runs); entry r * 27 + q is cell q of run r's
+// stencil.  A cell is numbered where it first appears, so the numbering needs
+// no atomics and is the same every time: an entry looks for the first earlier
+// run whose stencil holds its cell (a few tens of runs, 16 on the lattice).
+constexpr int MAXRUN = 64;
+constexpr uint16_t NO_ITEM = 0xffffu, ITEM_REF = 0x8000u;   // no particles; covered by entry (value & 0x7fff)
+struct StageTab {
+  uint32_t home[MAXRUN];
+  uint16_t id[2][27 * MAXRUN];       // the entry's item: fluid, solid
+  BlkItem item[2][STAGE_ITEMS];
+  uint32_t scan[BLOCK / WAVE], last[BLOCK / WAVE];
+};
+
+// Fills the table and writes the block's head and list; returns whether the
+// block's candidates fit.  nruns <= MAXRUN.
+__device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb, int lb, int nruns) {
+  const GLB uint32_t* rank = gpc<uint32_t>(S.rank);
+  const GLB uint32_t* st[2] = {gpc<uint32_t>(S.start_f), gpc<uint32_t>(S.start_s)};
+  const int n = 27 * nruns;
+  uint32_t done[2] = {0u, 0u};       // (cells << 21) | candidates numbered so far
+  bool big = false;
+  for (int i0 = 0; i0 < n; i0 += BLOCK) {
+    const int it = i0 + (int)threadIdx.x;
+    uint32_t f0[2] = {0u, 0u}, cnt[2] = {0u, 0u};
+    int ref = -1;
+    if (it < n) {
+      const int r = it / 27, q = it - 27 * r;
+      const uint32_t hc = tb.home[r];
+      const int x = (int)(hc & 1023u) + q % 3 - 1, y = (int)((hc >> 10) & 1023u) + (q / 3) % 3 - 1,
+                z = (int)(hc >> 20) + q / 9 - 1;
+      if (x >= 0 && y >= 0 && z >= 0 && x < S.dims[0] && y < S.dims[1] && z < S.dims[2]) {
+        for (int p = 0; p < r; ++p) {
+          const uint32_t h = tb.home[p];
+          const uint32_t dx = (uint32_t)(x - (int)(h & 1023u) + 1), dy = (uint32_t)(y - (int)((h >> 10) & 1023u) + 1),
+                         dz = (uint32_t)(z - (int)(h >> 20) + 1);
+          if (dx <= 2u && dy <= 2u && dz <= 2u) {
+            ref = p * 27 + (int)(dz * 9 + dy * 3 + dx);
+            break;
+          }
+        }
+        if (ref < 0) {
+          const uint32_t rk = rank[cell_linear(S, x, y, z)];
+#pragma unroll
+          for (int a = 0; a < 2; ++a) {
+            f0[a] = st[a][rk];
+            cnt[a] = st[a][rk + 1] - f0[a];
+            if (cnt[a] > 1023u) {
+              cnt[a] = 1023u;
+              big = true;
+            }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      uint32_t total;
+      const uint32_t at = done[a] + block_excl_scan((cnt[a] ? 1u << 21 : 0u) + cnt[a], tb.scan, total);
+      done[a] += total;
+      const uint32_t e = at >> 21;
+      if (it < n) tb.id[a][it] = ref >= 0 ? (uint16_t)(ITEM_REF | ref) : cnt[a] ? (uint16_t)e : NO_ITEM;
+      if (cnt[a] && e < (uint32_t)STAGE_ITEMS) tb.item[a][e] = BlkItem{f0[a], (uint16_t)at, (uint16_t)cnt[a]};
+    }
+  }
+  const int nc[2] = {(int)(done[0] & 0x1fffffu), (int)(done[1] & 0x1fffffu)};
+  const int ni[2] = {(int)(done[0] >> 21), (int)(done[1] >> 21)};
+  const int ns0 = (nc[0] + WAVE - 1) / WAVE * WAVE, nt = ns0 + nc[1];
+  const bool ok = !__syncthreads_or(big) && nt <= STAGE_CAP && ni[0] < STAGE_ITEMS && ni[1] < STAGE_ITEMS;
+  if (threadIdx.x == 0) S.bhead[lb] = BlkHead{ok ? nt : -1, ns0, {0, 0}};
+  if (!ok) return false;
+  uint32_t* list = S.blist + (int64_t)lb * STAGE_CAP;
+  if (nc[0] + (int)threadIdx.x < ns0) list[nc[0] + threadIdx.x] = 0u;
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    if (a && (int)threadIdx.x < ni[1]) tb.item[1][threadIdx.x].base += (uint16_t)ns0;
+    for (int it = threadIdx.x; it < n; it += BLOCK) {
+      const uint16_t v = tb.id[a][it];
+      if (v != NO_ITEM && (v & ITEM_REF)) tb.id[a][it] = tb.id[a][v & 0x7fffu];
+    }
+  }
+  __syncthreads();
+  // the list, sixteen lanes per cell
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+    for (int e = threadIdx.x >> 4; e < ni[a]; e += BLOCK / 16) {
+      const BlkItem x = tb.item[a][e];
+      for (int k = threadIdx.x & 15; k < x.cnt; k += 16) list[x.base + k] = x.start + (uint32_t)k;
+    }
+  return true;
+}
+
 template <class P>
 __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTab tab) {
 #pragma clang fp contract(off)
   typedef typename P::Pos Pos;
   typedef typename P::Pos4 Pos4;
   typedef typename P::Real4 Real4;
-  __shared__ uint32_t lds_pre[BLOCK / WAVE][2][32];
-  __shared__ uint32_t lds_beg[BLOCK / WAVE][2][32];
+  constexpr bool CANSTAGE = std::is_same<typename P::Real, float>::value;
+  __shared__ uint32_t lr_all[BLOCK / WAVE][6][32];
+  __shared__ StageTab tb;   // of the staged modes
   SLOT_PROLOGUE(DOM_FLUID);
   const int i = lb * BLOCK + threadIdx.x;
   const int nf = S.nf;
@@ -610,20 +751,48 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
   if (act) gp<Real4>(S.xo)[i] = cell_offset<P>(S, xi, yi, zi, c);
   const double cut2 = S.cut2;
   const int kf = S.kf, ks = S.ks;
+  // runs of equal cells among the block's particles, then the wave's
+  const uint32_t pc = pack_cell(c);
+  const uint32_t prevc = (uint32_t)__shfl_up((int)pc, 1, WAVE);
+  const int nact = __popcll(__ballot(act));
+  uint64_t runs = __ballot(act && (lane == 0 || prevc != pc));
+  bool staged = false;
+  int run = 0;
+  if constexpr (CANSTAGE) {
+    // the block's runs, numbered: a wave's first one may continue the last wave's
+    if (lane == WAVE - 1) tb.last[wv] = pc;
+    __syncthreads();
+    const bool cont = wv > 0 && tb.last[wv > 0 ? wv - 1 : 0] == (uint32_t)__builtin_amdgcn_readlane((int)pc, 0);
+    const uint64_t heads = cont ? runs & ~1ull : runs;
+    if (lane == 0) tb.scan[wv] = (uint32_t)__popcll(heads);
+    __syncthreads();
+    int nruns = 0;
+    for (int w = 0; w < BLOCK / WAVE; ++w) {
+      if (w < wv) run += (int)tb.scan[w];
+      nruns += (int)tb.scan[w];
+    }
+    run += __popcll(heads & (lane == WAVE - 1 ? ~0ull : (2ull << lane) - 1)) - 1;
+    if (nruns <= MAXRUN) {
+      if ((heads >> lane) & 1) tb.home[run] = pc;
+      __syncthreads();
+      staged = block_candidates(S, tb, lb, nruns);
+    } else if (threadIdx.x == 0) {
+      S.bhead[lb] = BlkHead{-1, 0, {0, 0}};
+    }
+  }
   GLB uint32_t* rows = gp<uint32_t>(S.rmaj);
   const GLB uint32_t* rank = gpc<uint32_t>(S.rank);
   const GLB uint32_t* stf = gpc<uint32_t>(S.start_f);
   const GLB uint32_t* sts = gpc<uint32_t>(S.start_s);
-  uint32_t* preF = lds_pre[wv][0];
-  uint32_t* preS = lds_pre[wv][1];
-  uint32_t* begF = lds_beg[wv][0];
-  uint32_t* begS = lds_beg[wv][1];
+  uint32_t (*lr)[32] = lr_all[wv];
+  uint32_t *preF = lr[0], *preS = lr[1], *begF = lr[2], *begS = lr[3], *lclF = lr[4], *lclS = lr[5];
   int cf = 0, cs = 0;
-  // runs of equal cells among the wave's particles
-  const uint32_t myr = rank[cell_linear(S, c[0], c[1], c[2])];
-  const uint32_t prevr = (uint32_t)__shfl_up((int)myr, 1, WAVE);
-  const int nact = __popcll(__ballot(act));
-  uint64_t runs = __ballot(act && (lane == 0 || prevr != myr));
+  // this particle as a row entry
+  uint32_t own = (uint32_t)i;
+  if (staged && act) {
+    const BlkItem x = tb.item[0][tb.id[0][27 * run + 13]];
+    own = 16u * (x.base + (uint32_t)i - x.start) | 4u * 13u << 16;
+  }
   // this lane's offset in a 27-cell stencil
   const int ox = lane % 3 - 1, oy = (lane / 3) % 3 - 1, oz = lane / 9 - 1;
   const int wbase = i - lane;
@@ -631,18 +800,34 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
     const int L = __builtin_ctzll(runs);
     runs &= runs - 1;
     const int R = runs ? __builtin_ctzll(runs) : nact;
-    const int dx = __builtin_amdgcn_readlane(c[0], L), dy = __builtin_amdgcn_readlane(c[1], L),
-              dz = __builtin_amdgcn_readlane(c[2], L);
-    const int nx = dx + ox, ny = dy + oy, nz = dz + oz;
-    const bool valid = lane < 27 && nx >= 0 && ny >= 0 && nz >= 0 && nx < S.dims[0] && ny < S.dims[1] &&
-                       nz < S.dims[2];
-    uint32_t f0 = 0, f1 = 0, s0 = 0, s1 = 0;
-    if (valid) {
-      const uint32_t r = rank[cell_linear(S, nx, ny, nz)];
-      f0 = stf[r];
-      f1 = stf[r + 1];
-      s0 = sts[r];
-      s1 = sts[r + 1];
+    uint32_t f0 = 0, f1 = 0, s0 = 0, s1 = 0, lf = 0, ls = 0;
+    if (staged) {
+      const int e = 27 * __builtin_amdgcn_readlane(run, L) + lane;
+      if (lane < 27) {
+        const uint32_t a = tb.id[0][e], b = tb.id[1][e];
+        if (a != NO_ITEM) {
+          const BlkItem x = tb.item[0][a];
+          f0 = x.start;
+          f1 = f0 + x.cnt;
+          lf = x.base;
+        }
+        if (b != NO_ITEM) {
+          const BlkItem x = tb.item[1][b];
+          s0 = x.start;
+          s1 = s0 + x.cnt;
+          ls = x.base;
+        }
+      }
+    } else {
+      const int nx = __builtin_amdgcn_readlane(c[0], L) + ox, ny = __builtin_amdgcn_readlane(c[1], L) + oy,
+                nz = __builtin_amdgcn_readlane(c[2], L) + oz;
+      if (lane < 27 && nx >= 0 && ny >= 0 && nz >= 0 && nx < S.dims[0] && ny < S.dims[1] && nz < S.dims[2]) {
+        const uint32_t r = rank[cell_linear(S, nx, ny, nz)];
+        f0 = stf[r];
+        f1 = stf[r + 1];
+        s0 = sts[r];
+        s1 = sts[r + 1];
+      }
     }
     uint32_t Mf, Ms;
     const uint32_t pf = wave_excl_scan(f1 - f0, &Mf);
@@ -652,10 +837,21 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
       begF[lane] = f0;
       preS[lane] = ps;
       begS[lane] = s0;
+      lclF[lane] = 16u * lf | 4u * (uint32_t)lane << 16;
+      lclS[lane] = 16u * ls | 4u * (uint32_t)lane << 16;
     }
     wave_lds_sync();
-    run_candidates<Pos>(xa, preF, begF, Mf, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, 0, kf, cf, true);
-    if (Ms) run_candidates<Pos>(xw, preS, begS, Ms, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, kf, ks, cs, false);
+    const uint32_t none = 0xfffffffeu;   // no solid candidate is the particle itself
+    if (staged) {
+      run_candidates<true, Pos>(xa, preF, begF, lclF, Mf, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, 0, kf, cf, own);
+      if (Ms)
+        run_candidates<true, Pos>(xw, preS, begS, lclS, Ms, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, kf, ks, cs, none);
+    } else {
+      run_candidates<false, Pos>(xa, preF, begF, nullptr, Mf, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, 0, kf, cf, own);
+      if (Ms)
+        run_candidates<false, Pos>(xw, preS, begS, nullptr, Ms, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, kf, ks, cs,
+                                   none);
+    }
     wave_lds_sync();
   }
   if (!act) return;
@@ -671,22 +867,33 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   const GLB uint32_t* RM = rows + (int64_t)i * (kf + ks);
-  GLB uint32_t* RS = gp<uint32_t>(S.nrec) + (int64_t)(i >> 6) * kf * WAVE + lane;
-  for (int k = 0; k < cf; k += 4) {
-    const u4 e = *(const GLB u4*)(RM + k);
-    const uint32_t ev[4] = {e.x, e.y, e.z, e.w};
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (k + u < cf) RS[(int64_t)(k + u) * WAVE] = ev[u];
-  }
-  RM += kf;
-  RS = gp<uint32_t>(S.srec) + (int64_t)(i >> 6) * ks * WAVE + lane;
-  for (int k = 0; k < cs; k += 4) {
-    const u4 e = *(const GLB u4*)(RM + k);
-    const uint32_t ev[4] = {e.x, e.y, e.z, e.w};
+  for (int a = 0; a < 2; ++a) {
+    const int cap = a ? ks : kf, n = a ? cs : cf;
+    GLB uint32_t* dst = gp<uint32_t>(a ? S.srec : S.nrec) + (int64_t)(i >> 6) * cap * WAVE;
+    if (a) RM += kf;
+    if (staged) {
+      // groups of four entries, filled up with the particle itself to a multiple
+      // of eight, and to eight at least: the sweeps fetch a row's first eight
+      // neighbours before they look at its length
+      GLB u4* G = (GLB u4*)dst + lane;
+      for (int k = 0; k < max(8, (n + 7) & ~7); k += 4) {
+        u4 e = *(const GLB u4*)(RM + k);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (k + u < cs) RS[(int64_t)(k + u) * WAVE] = ev[u];
+        for (int u = 0; u < 4; ++u)
+          if (k + u >= n) e[u] = own;
+        G[(int64_t)(k >> 2) * WAVE] = e;
+      }
+    } else {
+      GLB uint32_t* RS = dst + lane;
+      for (int k = 0; k < n; k += 4) {
+        const u4 e = *(const GLB u4*)(RM + k);
+        const uint32_t ev[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (k + u < n) RS[(int64_t)(k + u) * WAVE] = ev[u];
+      }
+    }
   }
 }
 
@@ -697,65 +904,126 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
 // pair's d^2 is formed exactly as in the cutoff test; the rows are walked in
 // order (fluid, then solid) so the sum is reproducible.
 // ---------------------------------------------------------------------------
-// In FP32 and mixed arithmetic the kernel sums are held to six waves per SIMD
-// (80 registers, two spilled): 3 us faster than at five, the step 8 us faster,
-// though the dummy-velocity sweep beside them stretches.  FP64 keeps the
-// compiler's budget.
-constexpr int sumw_min_waves(bool f64) { return f64 ? 1 : 6; }
 template <class P>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(
-    sumw_min_waves(std::is_same<typename P::Real, double>::value)))) void k_sumw(const SlotDesc* table,
-                                                                               LaunchTab tab) {
+__global__ __launch_bounds__(BLOCK) void k_sumw(const SlotDesc* table, LaunchTab tab) {
 #pragma clang fp contract(off)
   typedef typename P::Pos Pos;
   typedef typename P::Real Real;
   typedef typename P::Pos4 Pos4;
   typedef typename P::Real4 Real4;
-  __shared__ Pos4 wxa[WIN];
-  SLOT_PROLOGUE(DOM_FLUID);
+  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
+  // anchors of the staged candidates (three arrays of coordinates in FP64
+  // positions, records in FP32), or the window of the gathering rows
+  constexpr int STAGE_BYTES = CANSTAGE ? STAGE_CAP * (sizeof(Pos) == 8 ? 24 : 16) : 0;
+  constexpr int SMEM = STAGE_BYTES > WIN * (int)sizeof(Pos4) ? STAGE_BYTES : WIN * (int)sizeof(Pos4);
+  __shared__ __attribute__((aligned(32))) char smem[SMEM];
+  SLOT_FIND(DOM_FLUID);
   const int i = lb * BLOCK + threadIdx.x;
+  const int ii = min(i, S.nf - 1);
   const GLB Pos4* xa = gpc<Pos4>(S.xa);
+  const GLB Pos4* xw = gpc<Pos4>(S.xw);
+  BlkHead hd;
+  StageList sl;
+  if constexpr (CANSTAGE) {
+    hd = blk_head(S, lb);
+    sl = stage_list(S, lb);
+  }
+  const Pos4 xi4 = xa[ii];
+  const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
+  if (!live(S)) return;
+  const bool staged = CANSTAGE && hd.n >= 0;
+  Pos4* wxa = (Pos4*)smem;
   const Window win = window_of(lb, S.nf);
-  stage_window(wxa, xa, win);
+  Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
+  if constexpr (CANSTAGE) {
+    if (staged) {
+      ef = row_load(row_groups(S, ii), 0);
+      ew = row_load(wall_groups(S, ii), 0);
+      stage_candidates(
+          hd, sl, [&](bool sol, uint32_t j) { return (sol ? xw : xa)[j]; },
+          [&](uint32_t l, const Pos4& x, uint32_t) {
+            if constexpr (sizeof(Pos) == 8) {
+              Pos* X = (Pos*)smem;
+              X[l] = x.x;
+              X[STAGE_CAP + l] = x.y;
+              X[2 * STAGE_CAP + l] = x.z;
+            } else {
+              wxa[l] = x;
+            }
+          });
+    }
+  }
+  if (!staged) stage_window(wxa, xa, win);
   __syncthreads();
   if (i >= S.nf) return;
-  const Pos4 xi4 = xa[i];
   const Pos xi = xi4.x, yi = xi4.y, zi = xi4.z;
   const double inv_h = 1.0 / S.h, kW = S.kW;
   double sw = kW;   // W(0)
   const int lane = i & (WAVE - 1);
   const int64_t slice = i >> 6;
-  {
-    const int n = (int)S.nfc[i];
+  auto add = [&](const Pos xj, const Pos yj, const Pos zj, bool real) {
+    const Pos ddx = xi - xj, ddy = yi - yj, ddz = zi - zj;
+    const Pos s2 = ddx * ddx + ddy * ddy;
+    const Pos d2 = s2 + ddz * ddz;
+    const double w = kernel_W_d2((double)d2, inv_h, kW);
+    if (real) sw += w;
+  };
+  if (staged) {
+    // the fluid row, then the wall row, of the staged candidates
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      const GLB u4* G = a ? wall_groups(S, i) : row_groups(S, i);
+      Row8 r = a ? ew : ef;
+      const int n = a ? nw : nn;
+      auto group = [&](int k, auto whole) {
+        uint32_t e[8];
+        row_entries(r, e);
+        if (k + 8 < n) r = row_load(G, k + 8);
+        Pos x[8], y[8], z[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if constexpr (sizeof(Pos) == 8) {
+            const char* q = smem + ((e[u] & 0xffffu) >> 1);
+            x[u] = *(const Pos*)q;
+            y[u] = *(const Pos*)(q + 8 * STAGE_CAP);
+            z[u] = *(const Pos*)(q + 16 * STAGE_CAP);
+          } else {
+            const Pos4 o = *(const Pos4*)(smem + (e[u] & 0xffffu));
+            x[u] = o.x;
+            y[u] = o.y;
+            z[u] = o.z;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) add(x[u], y[u], z[u], decltype(whole)::value || k + u < n);
+      };
+      int k = 0;
+      for (; k + 8 <= n; k += 8) group(k, std::true_type{});
+      if (k < n) group(k, std::false_type{});
+    }
+  } else {
     const GLB uint32_t* R = gpc<uint32_t>(S.nrec) + slice * (int64_t)S.kf * WAVE + lane;
     uint32_t jn[ROW_UNROLL];
 #pragma unroll
     for (int u = 0; u < ROW_UNROLL; ++u) jn[u] = ldnt(R + (int64_t)u * WAVE);
-    for (int k = 0; k < n; k += ROW_UNROLL) {
+    for (int k = 0; k < nn; k += ROW_UNROLL) {
       Pos4 xj[ROW_UNROLL];
 #pragma unroll
-      for (int u = 0; u < ROW_UNROLL; ++u) xj[u] = win_get(wxa, xa, k + u < n ? jn[u] : (uint32_t)i, win);
-      if (k + ROW_UNROLL < n) {
+      for (int u = 0; u < ROW_UNROLL; ++u) xj[u] = win_get(wxa, xa, k + u < nn ? jn[u] : (uint32_t)i, win);
+      if (k + ROW_UNROLL < nn) {
 #pragma unroll
         for (int u = 0; u < ROW_UNROLL; ++u) jn[u] = ldnt(R + (int64_t)(k + ROW_UNROLL + u) * WAVE);
       }
 #pragma unroll
-      for (int u = 0; u < ROW_UNROLL; ++u) {
-        const Pos ddx = xi - xj[u].x, ddy = yi - xj[u].y, ddz = zi - xj[u].z;
-        const Pos s2 = ddx * ddx + ddy * ddy;
-        const Pos d2 = s2 + ddz * ddz;
-        const double w = kernel_W_d2((double)d2, inv_h, kW);
-        if (k + u < n) sw += w;
-      }
+      for (int u = 0; u < ROW_UNROLL; ++u) add(xj[u].x, xj[u].y, xj[u].z, k + u < nn);
     }
   }
   GLB Real4* vr = gp<Real4>(S.vr);
   Real4 v = vr[i];
   const double dp3 = S.dp * S.dp * S.dp;
-  {
-    const int n = (int)S.nsc[i];
+  if (!staged) {
+    const int n = nw;
     const GLB uint32_t* R = gpc<uint32_t>(S.srec) + slice * (int64_t)S.ks * WAVE + lane;
-    const GLB Pos4* xw = gpc<Pos4>(S.xw);
     uint32_t wn[SOLID_UNROLL];
 #pragma unroll
     for (int u = 0; u < SOLID_UNROLL; ++u) wn[u] = ldnt(R + (int64_t)u * WAVE);
@@ -768,13 +1036,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(
         for (int u = 0; u < SOLID_UNROLL; ++u) wn[u] = ldnt(R + (int64_t)(k + SOLID_UNROLL + u) * WAVE);
       }
 #pragma unroll
-      for (int u = 0; u < SOLID_UNROLL; ++u) {
-        const Pos ddx = xi - xq[u].x, ddy = yi - xq[u].y, ddz = zi - xq[u].z;
-        const Pos s2 = ddx * ddx + ddy * ddy;
-        const Pos d2 = s2 + ddz * ddz;
-        const double w = kernel_W_d2((double)d2, inv_h, kW);
-        if (k + u < n) sw += w;
-      }
+      for (int u = 0; u < SOLID_UNROLL; ++u) add(xq[u].x, xq[u].y, xq[u].z, k + u < n);
     }
   }
   S.sumW[i] = sw;
@@ -783,33 +1045,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(
   const double rn = S.free_surface ? fmax(rcur, rre) : rre;
   v.w = P::kRel ? (Real)(rn - S.rho0) : (Real)rn;
   vr[i] = v;
-}
-
-// Sum over the wavefront by DPP lane moves (no LDS traffic), in a fixed
-// order: pairs, quads, half-rows and rows of 16 by quad and mirror
-// permutations, then row 1 and row 3 take the row before them (row_bcast:15)
-// and rows 2 and 3 the first 32 lanes' sum (row_bcast:31).  The total is in
-// lane 63; every lane must be active.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_take(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, false));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_take(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xf, false);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xf, false);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-template <class Real>
-__device__ __forceinline__ Real wave_total(Real v) {
-  v += dpp_take<0xb1, 0xf>(v);    // quad_perm [1,0,3,2]
-  v += dpp_take<0x4e, 0xf>(v);    // quad_perm [2,3,0,1]
-  v += dpp_take<0x141, 0xf>(v);   // row_half_mirror
-  v += dpp_take<0x140, 0xf>(v);   // row_mirror
-  v += dpp_take<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-  v += dpp_take<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-  return rl(v, WAVE - 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -956,6 +1191,10 @@ __global__ __launch_bounds__(BLOCK) void k_wallvel(const SlotDesc* table, Launch
     o.w = (Real)((double)acc[3] * (S.dp * S.dp * S.dp));
   }
   gp<Real4>(S.vd)[w] = o;
+  if constexpr (std::is_same<Real, float>::value) {   // the staged sweeps' record
+    o.w = gpc<Real4>(S.lev)[w].w;   // the body
+    gp<Real4>(S.vdb)[w] = o;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1137,34 +1376,84 @@ __device__ __forceinline__ void grad_add(Real* G, Real c, Real dx, Real dy, Real
 // density, the (T, Drho) record the reorder wrote) instead of the five of
 // the separate launches.
 // ---------------------------------------------------------------------------
-// The fused variant without dissipation is held to three waves per SIMD in
-// FP32 and mixed arithmetic (168 registers, 20 bytes spilled per lane): the
-// few spills cost less than the latency hiding the third wave brings.  The
-// FP64 and dissipation variants keep the compiler's budget (held down they
-// spill 100-400 bytes per lane and run slower).
-constexpr int visc_min_waves(bool mom0, bool diss, bool f64) { return mom0 && !diss && !f64 ? 3 : 1; }
+// The staged candidates leave two waves per SIMD: their 256 registers are the
+// budget in FP32 and mixed arithmetic (FP64 keeps the compiler's).
+constexpr int visc_min_waves(bool f64) { return f64 ? 1 : 2; }
 template <class P, bool DISS, bool MAT, bool MOM0>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(
-    visc_min_waves(MOM0, DISS, std::is_same<typename P::Real, double>::value))))
-void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
+__global__ __launch_bounds__(BLOCK)
+    __attribute__((amdgpu_waves_per_eu(visc_min_waves(std::is_same<typename P::Real, double>::value)))) void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
   typedef typename P::Real Real;
   typedef typename P::Temp Temp;
   typedef typename P::Real4 Real4;
-  __shared__ double lds[4 * NB * 7];
-  __shared__ double lds_p[MOM0 ? 4 * NB * 6 : 1];
+  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
+  // staged candidates, then (after the rows) the block reductions
+  constexpr int RED_BYTES = 4 * NB * (7 + (MOM0 ? 6 : 0)) * 8;
+  __shared__ __attribute__((aligned(32))) char smem[CANSTAGE ? STAGE_CAP * 32 : RED_BYTES];
+  __shared__ float shift[CANSTAGE ? 3 * SHIFT_LD : 1];
+  double* lds = (double*)smem;
+  double* lds_p = lds + 4 * NB * 7;
   __shared__ double lds_d[BLOCK / WAVE];
   __shared__ Real Ktab[MAT ? NMAT * NMAT : 1];
-  SLOT_PROLOGUE(DOM_FLUID);
+  __shared__ Real Kwall[(MAT ? NMAT : 1) * NB];   // K_iw of eq. 22 per material and body
+  __shared__ Temp Tb[NB];
+  SLOT_FIND(DOM_FLUID);
+  const int nf = S.nf;
+  const int i = lb * BLOCK + threadIdx.x;
+  const int ii = min(i, nf - 1);
+  const GLB Real4* vr = gpc<Real4>(S.vr);
+  const GLB Temp* T = gpc<Temp>(S.T);
+  const GLB Real4* xo = gpc<Real4>(S.xo);
+  const GLB TempRate<P>* td = gpc<TempRate<P>>(S.td);
+  const GLB Real4* vdw = gpc<Real4>(S.vd);   // dummy velocity of eq. 18
+  const GLB Real4* vw = gpc<Real4>(S.vw);    // rigid velocity (velocity gradient of eq. 23)
+  const GLB Real4* lv = gpc<Real4>(S.lev);
+  BlkHead hd;
+  StageList sl;
+  if constexpr (CANSTAGE) {
+    hd = blk_head(S, lb);
+    sl = stage_list(S, lb);
+  }
+  const Real4 vi = vr[ii];
+  const Real4 oi = xo[ii];
+  const Temp Ti = T[ii];
+  const Real drhoi = gpc<Real>(S.drho)[ii];
+  const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
+  if (!live(S)) return;
+  const bool staged = CANSTAGE && hd.n >= 0;
   const bool mats = MAT && S.mat != nullptr;
+  Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
+  if constexpr (CANSTAGE) {
+    if (staged) {
+      ef = row_load(row_groups(S, ii), 0);
+      ew = row_load(wall_groups(S, ii), 0);
+      shift_table(shift, (float)S.cs_r);
+      const GLB f4* so = gpc<f4>(S.so);
+      const GLB f4* vdb = gpc<f4>(S.vdb);
+      // the position record's fourth word takes the sorted index, at which the
+      // temperature record or the lever arm is gathered
+      stage_candidates(
+          hd, sl, [&](bool sol, uint32_t j) { return RecPair{(sol ? so : xo)[j], (sol ? vdb : vr)[j]}; },
+          [&](uint32_t l, const RecPair& r, uint32_t j) {
+            f4 o = r.a;
+            o.w = pack_index(j, 0.0f);
+            *(f4*)(smem + 16 * l) = o;
+            *(f4*)(smem + 16 * l + 16 * STAGE_CAP) = r.b;
+          });
+    }
+  }
   if (mats) {
     for (int q = threadIdx.x; q < NMAT * NMAT; q += BLOCK) {
       const double ka = S.mk[q / NMAT], kb = S.mk[q % NMAT];
       Ktab[q] = (Real)(4.0 * ka * kb / (ka + kb));
     }
-    __syncthreads();
   }
-  const int nf = S.nf;
-  const int i = lb * BLOCK + threadIdx.x;
+  for (int q = threadIdx.x; q < (mats ? NMAT : 1) * S.nbody; q += BLOCK) {
+    const int b = q % S.nbody, mq = q / S.nbody;
+    const double k = mats ? S.mk[mq] : S.k_f;
+    Kwall[mq * NB + b] = (Real)(4.0 * k * S.bk[b] / (k + S.bk[b]));
+    if (mq == 0) Tb[b] = (Temp)S.bT[b];
+  }
+  __syncthreads();
   const size_t nbf = (size_t)S.nblk[DOM_FLUID];
   if (threadIdx.x < NB * 6) S.press_part[(size_t)threadIdx.x * nbf + lb] = 0.0;
   BodyAcc<7> acc;
@@ -1174,22 +1463,14 @@ void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
   bool wall = false;
   double vphi = 0.0;   // V_i Phi_i
   if (i < nf) {
-    const GLB Real4* vr = gpc<Real4>(S.vr);
-    const GLB Temp* T = gpc<Temp>(S.T);
-    const GLB Real4* xo = gpc<Real4>(S.xo);
-    const GLB Real* drho = gpc<Real>(S.drho);
-    const GLB TempRate<P>* td = gpc<TempRate<P>>(S.td);
     const Real m = (Real)S.mass;
     const Real inv_h = (Real)(1.0 / S.h), kF = (Real)S.kF, csr = (Real)S.cs_r;
-    const Real4 vi = vr[i];
-    const Real4 oi = xo[i];
     const uint32_t ci = unpack_index(oi.w);
     const Real rhoi = rho_abs<P>(S, vi.w);
-    const Temp Ti = T[i];
     const Real c2 = (Real)(2.0 * S.eta) * rcp(rhoi);   // 2 eta V_i / m_i
     const Real Kff = (Real)(4.0 * S.k_f * S.k_f / (S.k_f + S.k_f));
     const uint32_t mi = mats ? S.mat[i] : 0u;
-    const double kI = mats ? S.mk[mi] : S.k_f, cpI = mats ? S.mcp[mi] : S.cp_f;
+    const double cpI = mats ? S.mcp[mi] : S.cp_f;
     Real ax = 0, ay = 0, az = 0, hs = 0;
     Real G[9];
 #pragma unroll
@@ -1200,7 +1481,7 @@ void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
     Real px = 0, py = 0, pz = 0;
     if constexpr (MOM0) {
       hdt = (Real)(0.5 * S.ctl->dt);
-      wih = vi.w + hdt * drho[i];
+      wih = fma(hdt, drhoi, vi.w);
       rhoih = rho_abs<P>(S, wih);
       pih = press<P>(S, wih);
       c2p = (Real)2 * rcp(rhoih);
@@ -1208,16 +1489,150 @@ void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
     }
     const int lane = i & (WAVE - 1);
     const int64_t slice = i >> 6;
-    {
-      const int n = (int)S.nfc[i];
+    const Real cc2 = (Real)(S.c0 * S.c0);
+    // one fluid pair: its vector, the neighbour's state, temperature, density
+    // rate and material
+    auto pair = [&](Real rx, Real ry, Real rz, const Real4& vj, Temp Tj, Real dj, uint32_t mj, bool real) {
+      const Real r2 = dot_fma(rx, ry, rz, rx, ry, rz), rs = rsq0(r2);
+      Real Fk = kernel_F(r2, rs, inv_h, kF);
+      Fk = real ? Fk : (Real)0;
+      const Real Vj = m * rcp(rho_abs<P>(S, vj.w));
+      const Real cv = c2 * Vj * Fk;
+      const Real dx = vi.x - vj.x, dy = vi.y - vj.y, dz = vi.z - vj.z;
+      ax = fma(cv, dx, ax);
+      ay = fma(cv, dy, ay);
+      az = fma(cv, dz, az);
+      const Real Kij = mats ? Ktab[mi * NMAT + mj] : Kff;
+      hs = fma(Vj * Kij * (Real)(Ti - Tj), Fk, hs);
+      if (DISS) grad_add(G, Vj * Fk, -dx, -dy, -dz, rx, ry, rz);
+      if constexpr (MOM0) {
+        // eq. 10-12 at the half-step densities, velocities of the step's start
+        const Real wjh = fma(hdt, dj, vj.w);
+        const Real sp = mom_factor<P>(S, rhoih, pih, -c2p, c0, cc2, m * rcp(rho_abs<P>(S, wjh)),
+                                      dot_fma(dx, dy, dz, rx, ry, rz), rs, wjh, Fk);
+        px = fma(sp, rx, px);
+        py = fma(sp, ry, py);
+        pz = fma(sp, rz, pz);
+      }
+    };
+    // one wall pair: its vector, the dummy velocity, the body, the lever arm
+    // and the rigid velocity
+    const Real Vw = (Real)S.vol_w;
+    const Real rc = rcp(rhoi * (Real)cpI);
+    const Real gx0 = (Real)S.g[0], gy0 = (Real)S.g[1], gz0 = (Real)S.g[2];
+    const Real rho0 = (Real)S.rho0, ic02 = (Real)(1.0 / (S.c0 * S.c0));
+    auto wpair = [&](Real rx, Real ry, Real rz, const Real4& vq, int b, const Real4& lq, const Real4& vg, bool real) {
+#pragma clang fp contract(off)
+      const Real r2 = dot_fma(rx, ry, rz, rx, ry, rz);
+      Real Fk = kernel_F(r2, rsq0(r2), inv_h, kF);
+      Fk = real ? Fk : (Real)0;
+      const Real cv = c2 * Vw * Fk;
+      const Real dx = vi.x - vq.x, dy = vi.y - vq.y, dz = vi.z - vq.z;
+      ax = fma(cv, dx, ax);
+      ay = fma(cv, dy, ay);
+      az = fma(cv, dz, az);
+      const Real tk = Vw * Kwall[mi * NB + b] * (Real)(Ti - Tb[b]);
+      hs = fma(tk, Fk, hs);
+      if (DISS) grad_add(G, Vw * Fk, vg.x - vi.x, vg.y - vi.y, vg.z - vi.z, rx, ry, rz);
+      acc.moment(cv * dx, cv * dy, cv * dz, lq);
+      acc.v0[6] += (double)(rc * (tk * Fk));
+      if constexpr (MOM0) {
+        const Real sp = wall_factor(rhoih, pih, c2p, Vw, rho0, ic02, dot_fma(gx0, gy0, gz0, rx, ry, rz), Fk);
+        px = fma(sp, rx, px);
+        py = fma(sp, ry, py);
+        pz = fma(sp, rz, pz);
+        pacc.moment(sp * rx, sp * ry, sp * rz, lq);
+      }
+    };
+    wall = nw > 0;
+    if (staged) {
+      if constexpr (CANSTAGE) {
+        // as staged_row, with the temperature records of a set gathered (at the
+        // sorted index in its position record) while the set before is used
+        const GLB u4* Gr = row_groups(S, i);
+        struct Temps {
+          Temp T[4];
+          Real d[4];
+          uint32_t m[4];
+        };
+        auto gather = [&](Temps& t, const Set4& q) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const uint32_t j = unpack_index(q.o[u].w);
+            if constexpr (MOM0) {
+              t.T[u] = td[j].T;
+              t.d[u] = td[j].d;
+            } else {
+              t.T[u] = T[j];
+              t.d[u] = 0;
+            }
+            t.m[u] = mats ? S.mat[j] : 0u;
+          }
+        };
+        auto use = [&](const Set4& q, const Temps& t) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            Real rx, ry, rz;
+            set_vec(q, u, oi, rx, ry, rz);
+            pair(rx, ry, rz, q.v[u], t.T[u], t.d[u], t.m[u], true);
+          }
+        };
+        Row8 rn = ef;
+        if (8 < nn) rn = row_load(Gr, 8);
+        Set4 A, B;
+        Temps ta, tb;
+        set_fetch(A, ef.a, smem, shift);
+        set_fetch(B, ef.b, smem, shift);
+        gather(ta, A);
+        for (int k = 0; k < nn; k += 8) {
+          gather(tb, B);
+          Row8 rl = rn;
+          if (k + 16 < nn) rl = row_load(Gr, k + 16);
+          __builtin_amdgcn_sched_barrier(0);
+          use(A, ta);
+          set_fetch(A, rn.a, smem, shift);
+          gather(ta, A);
+          __builtin_amdgcn_sched_barrier(0);
+          use(B, tb);
+          set_fetch(B, rn.b, smem, shift);
+          rn = rl;
+        }
+        staged_wall(wall_groups(S, i), ew, nw, smem, shift, [&](const Set4& W, const bool(&real)[4]) {
+          const float w[4] = {W.v[0].w, W.v[1].w, W.v[2].w, W.v[3].w};
+          int b[4];
+          f4 lq[4], vg[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            lq[u] = vg[u] = f4(0);
+            if (real[u]) {
+              const uint32_t j = unpack_index(W.o[u].w);
+              lq[u] = lv[j];
+              if (DISS) vg[u] = vw[j];
+            }
+          }
+          const bool one = acc.current(w, real, b);
+          if (MOM0 && pacc.id0 < 0) pacc.id0 = acc.id0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (!one) {
+              if (!acc.select(b[u])) raise_flag(S, F_CAPACITY);
+              if (MOM0) pacc.select(b[u]);
+            }
+            Real rx, ry, rz;
+            set_vec(W, u, oi, rx, ry, rz);
+            wpair(rx, ry, rz, W.v[u], b[u], lq[u], vg[u], real[u]);
+          }
+        });
+      }
+    } else {
       const GLB uint32_t* R = gpc<uint32_t>(S.nrec) + slice * (int64_t)S.kf * WAVE + lane;
       uint32_t jn[ROW_UNROLL];
 #pragma unroll
       for (int u = 0; u < ROW_UNROLL; ++u) jn[u] = ldnt(R + (int64_t)u * WAVE);
-      for (int k = 0; k < n; k += ROW_UNROLL) {
+      for (int k = 0; k < nn; k += ROW_UNROLL) {
         uint32_t j[ROW_UNROLL];
 #pragma unroll
-        for (int u = 0; u < ROW_UNROLL; ++u) j[u] = k + u < n ? jn[u] : (uint32_t)i;
+        for (int u = 0; u < ROW_UNROLL; ++u) j[u] = k + u < nn ? jn[u] : (uint32_t)i;
         Real4 vj[ROW_UNROLL], oj[ROW_UNROLL];
         Temp Tj[ROW_UNROLL];
         Real dj[ROW_UNROLL];
@@ -1230,9 +1645,10 @@ void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
             dj[u] = td[j[u]].d;
           } else {
             Tj[u] = T[j[u]];
+            dj[u] = 0;
           }
         }
-        if (k + ROW_UNROLL < n) {
+        if (k + ROW_UNROLL < nn) {
 #pragma unroll
           for (int u = 0; u < ROW_UNROLL; ++u) jn[u] = ldnt(R + (int64_t)(k + ROW_UNROLL + u) * WAVE);
         }
@@ -1240,99 +1656,41 @@ void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
         for (int u = 0; u < ROW_UNROLL; ++u) {
           Real rx, ry, rz;
           pair_vec(oi, ci, oj[u], csr, rx, ry, rz);
-          const Real r2 = rx * rx + ry * ry + rz * rz;
-          const Real Fk = k + u < n ? kernel_F(r2, inv_h, kF) : (Real)0;
-          const Real Vj = m * rcp(rho_abs<P>(S, vj[u].w));
-          const Real cv = c2 * Vj * Fk;
-          ax += cv * (vi.x - vj[u].x);
-          ay += cv * (vi.y - vj[u].y);
-          az += cv * (vi.z - vj[u].z);
-          const Real Kij = mats ? Ktab[mi * NMAT + S.mat[j[u]]] : Kff;
-          hs += Vj * Kij * (Real)(Ti - Tj[u]) * Fk;
-          if (DISS) grad_add(G, Vj * Fk, vj[u].x - vi.x, vj[u].y - vi.y, vj[u].z - vi.z, rx, ry, rz);
-          if constexpr (MOM0) {
-            // eq. 10-12 at the half-step densities, velocities of the step's start
-            const Real inv = r2 > (Real)0 ? rsq(r2) : (Real)0;
-            const Real wjh = vj[u].w + hdt * dj[u];
-            const Real rhoj = rho_abs<P>(S, wjh);
-            const Real pj = press<P>(S, wjh);
-            const Real dU = -((vi.x - vj[u].x) * rx + (vi.y - vj[u].y) * ry + (vi.z - vj[u].z) * rz) * inv;
-            const Real beta = fmin((Real)3 * fmax(dU, (Real)0), c0);
-            const Real ps = (Real)0.5 * (pih + pj) + rhoih * rhoj * beta * dU * rcp(rhoih + rhoj);
-            const Real sp = -c2p * (m * rcp(rhoj)) * ps * Fk;
-            px += sp * rx;
-            py += sp * ry;
-            pz += sp * rz;
-          }
+          pair(rx, ry, rz, vj[u], Tj[u], dj[u], mats ? S.mat[j[u]] : 0u, k + u < nn);
         }
       }
-    }
-    {
-      const int n = (int)S.nsc[i];
-      wall = n > 0;
-      const GLB uint32_t* R = gpc<uint32_t>(S.srec) + slice * (int64_t)S.ks * WAVE + lane;
+      R = gpc<uint32_t>(S.srec) + slice * (int64_t)S.ks * WAVE + lane;
       const GLB Real4* so = gpc<Real4>(S.so);
-      const GLB Real4* vdw = gpc<Real4>(S.vd);   // dummy velocity of eq. 18
-      const GLB Real4* vw = gpc<Real4>(S.vw);    // rigid velocity (velocity gradient of eq. 23)
-      const GLB Real4* lv = gpc<Real4>(S.lev);
-      const Real Vw = (Real)S.vol_w;
-      const Real rc = rcp(rhoi * (Real)cpI);
       uint32_t wn[VISC_SOLID_UNROLL];
 #pragma unroll
       for (int u = 0; u < VISC_SOLID_UNROLL; ++u) wn[u] = ldnt(R + (int64_t)u * WAVE);
-      for (int k0 = 0; k0 < n; k0 += VISC_SOLID_UNROLL) {
+      for (int k0 = 0; k0 < nw; k0 += VISC_SOLID_UNROLL) {
         Real4 owu[VISC_SOLID_UNROLL], vqu[VISC_SOLID_UNROLL], lqu[VISC_SOLID_UNROLL], vgu[VISC_SOLID_UNROLL];
 #pragma unroll
         for (int u = 0; u < VISC_SOLID_UNROLL; ++u) {
-          const uint32_t w = k0 + u < n ? wn[u] : 0u;
+          const uint32_t w = k0 + u < nw ? wn[u] : 0u;
           owu[u] = so[w];
           vqu[u] = vdw[w];
           lqu[u] = lv[w];
           if (DISS) vgu[u] = vw[w];
         }
-        if (k0 + VISC_SOLID_UNROLL < n) {
+        if (k0 + VISC_SOLID_UNROLL < nw) {
 #pragma unroll
           for (int u = 0; u < VISC_SOLID_UNROLL; ++u) wn[u] = ldnt(R + (int64_t)(k0 + VISC_SOLID_UNROLL + u) * WAVE);
         }
 #pragma unroll
         for (int u = 0; u < VISC_SOLID_UNROLL; ++u) {
-        if (k0 + u >= n) break;
-        const Real4 ow = owu[u], vq = vqu[u], lq = lqu[u];
-        Real rx, ry, rz;
-        pair_vec(oi, ci, ow, csr, rx, ry, rz);
-        const Real Fk = kernel_F(rx * rx + ry * ry + rz * rz, inv_h, kF);
-        const int b = (int)lq.w;
-        const Real cv = c2 * Vw * Fk;
-        const Real fx = cv * (vi.x - vq.x), fy = cv * (vi.y - vq.y), fz = cv * (vi.z - vq.z);
-        ax += fx;
-        ay += fy;
-        az += fz;
-        const Real Kiw = (Real)(4.0 * kI * S.bk[b] / (kI + S.bk[b]));
-        const Real term = Vw * Kiw * (Real)(Ti - (Temp)S.bT[b]) * Fk;
-        hs += term;
-        if (DISS) grad_add(G, Vw * Fk, vgu[u].x - vi.x, vgu[u].y - vi.y, vgu[u].z - vi.z, rx, ry, rz);
-        // force of the fluid on the body is -m_i times this pair's acceleration
-        const double gx = -(double)m * fx, gy = -(double)m * fy, gz = -(double)m * fz;
-        const double lx = lq.x, ly = lq.y, lz = lq.z;
-        const double contrib[7] = {gx, gy, gz, ly * gz - lz * gy, lz * gx - lx * gz, lx * gy - ly * gx,
-                                   (double)m * cpI * (double)(rc * term)};
-        if (!acc.add(b, contrib)) raise_flag(S, F_CAPACITY);
-        if constexpr (MOM0) {
-          // the wall pressure of the one-sided Riemann problem (eq. 16-19)
-          const Real PR = pih - rhoih * ((Real)S.g[0] * rx + (Real)S.g[1] * ry + (Real)S.g[2] * rz);
-          const Real rhoR = (Real)S.rho0 + PR * (Real)(1.0 / (S.c0 * S.c0));
-          const Real ps = (rhoih * PR + rhoR * pih) * rcp(rhoih + rhoR);
-          const Real sp = -c2p * Vw * ps * Fk;
-          const Real qx = sp * rx, qy = sp * ry, qz = sp * rz;
-          px += qx;
-          py += qy;
-          pz += qz;
-          const double hx = -(double)m * qx, hy = -(double)m * qy, hz = -(double)m * qz;
-          const double pc[6] = {hx, hy, hz, ly * hz - lz * hy, lz * hx - lx * hz, lx * hy - ly * hx};
-          if (!pacc.add(b, pc)) raise_flag(S, F_CAPACITY);
-        }
+          if (k0 + u >= nw) break;
+          Real rx, ry, rz;
+          pair_vec(oi, ci, owu[u], csr, rx, ry, rz);
+          const int b = (int)lqu[u].w;
+          if (!acc.select(b)) raise_flag(S, F_CAPACITY);
+          if (MOM0) pacc.select(b);
+          wpair(rx, ry, rz, vqu[u], b, lqu[u], vgu[u], true);
         }
       }
+    }
+    {
       if (DISS && S.diss) {
         // Phi = 2 eta S:S with S = (G + G^T)/2
         const Real sxy = (Real)0.5 * (G[1] + G[3]), sxz = (Real)0.5 * (G[2] + G[6]),
@@ -1370,6 +1728,15 @@ void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
       }
     }
   }
+  acc.to_force((double)(Real)S.mass);
+  pacc.to_force((double)(Real)S.mass);
+  {
+    // heat flows from the sums of dT/dt
+    const uint32_t mi = mats && i < nf ? S.mat[i] : 0u;
+    const double mc = (double)(Real)S.mass * (mats ? S.mcp[mi] : S.cp_f);
+    acc.v0[6] *= mc;
+    acc.v1[6] *= mc;
+  }
   if (__syncthreads_or(wall)) {
     block_body_reduce<7>(acc, S.nbody, S.visc_part, nbf, lb, false, lds);
     if constexpr (MOM0) block_body_reduce<6>(pacc, S.nbody, S.press_part, nbf, lb, true, lds_p);
@@ -1399,7 +1766,7 @@ __global__ __launch_bounds__(BLOCK) void k_half_a(const SlotDesc* table, LaunchT
   const Real hdt = (Real)(0.5 * S.ctl->dt);
   GLB Real4* vr = gp<Real4>(S.vr);
   Real4 v = vr[i];
-  v.w += hdt * gpc<Real>(S.drho)[i];
+  v.w = fma(hdt, gpc<Real>(S.drho)[i], v.w);
   vr[i] = v;
   GLB Real4* dr = gp<Real4>(S.drift);
   Real4 d = dr[i];
@@ -1407,6 +1774,27 @@ __global__ __launch_bounds__(BLOCK) void k_half_a(const SlotDesc* table, LaunchT
   d.y += hdt * v.y;
   d.z += hdt * v.z;
   dr[i] = d;
+}
+
+// Stages the candidates of a momentum or continuity sweep: cell-relative
+// positions with the particle's volume m / rho as the fourth component, then
+// the records b (fluid: velocity and density) and ws (solid) at 16 * STAGE_CAP,
+// and the shift table.  The caller synchronises.
+template <class P>
+__device__ __forceinline__ void stage_pairs(const SlotDesc& S, const BlkHead& hd, const StageList& sl, const GLB f4* b,
+                                            const GLB f4* ws, char* smem, float* shift) {
+  const GLB f4* xo = gpc<f4>(S.xo);
+  const GLB f4* so = gpc<f4>(S.so);
+  const float m = (float)S.mass;
+  shift_table(shift, (float)S.cs_r);
+  stage_candidates(
+      hd, sl, [&](bool sol, uint32_t j) { return RecPair{(sol ? so : xo)[j], (sol ? ws : b)[j]}; },
+      [&](uint32_t l, const RecPair& r, uint32_t) {
+        f4 o = r.a;
+        o.w = m * rcp(rho_abs<P>(S, r.b.w));
+        *(f4*)(smem + 16 * l) = o;
+        *(f4*)(smem + 16 * l + 16 * STAGE_CAP) = r.b;
+      });
 }
 
 // ---------------------------------------------------------------------------
@@ -1419,46 +1807,110 @@ template <class P>
 __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, LaunchTab tab, int sub) {
   typedef typename P::Real Real;
   typedef typename P::Real4 Real4;
-  __shared__ double lds[4 * NB * 6];
-  SLOT_PROLOGUE(DOM_FLUID);
-  if (sub >= S.ctl->n_ac) return;
+  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
+  // staged candidates, then (after the rows) the block reduction
+  __shared__ __attribute__((aligned(32))) char smem[CANSTAGE ? STAGE_CAP * 32 : 4 * NB * 6 * 8];
+  __shared__ float shift[CANSTAGE ? 3 * SHIFT_LD : 1];
+  double* lds = (double*)smem;
+  SLOT_FIND(DOM_FLUID);
   const int nf = S.nf;
   const int i = lb * BLOCK + threadIdx.x;
+  const int ii = min(i, nf - 1);
   const GLB Real4* vr = gpc<Real4>(S.vr);
   const GLB Real4* xo = gpc<Real4>(S.xo);
+  const GLB Real4* lv = gpc<Real4>(S.lev);
+  BlkHead hd;
+  StageList sl;
+  if constexpr (CANSTAGE) {
+    hd = blk_head(S, lb);
+    sl = stage_list(S, lb);
+  }
+  const Real4 vi = vr[ii];
+  const Real4 oi = xo[ii];
+  const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
+  if (!live_sub(S, sub)) return;
+  const bool staged = CANSTAGE && hd.n >= 0;
+  Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
+  if constexpr (CANSTAGE) {
+    if (staged) {
+      ef = row_load(row_groups(S, ii), 0);
+      ew = row_load(wall_groups(S, ii), 0);
+      stage_pairs<P>(S, hd, sl, vr, lv, smem, shift);
+      __syncthreads();
+    }
+  }
   BodyAcc<6> acc;
   acc.init();
   bool wall = false;
   if (i < nf) {
     const Real c0 = (Real)S.c0;
     const Real m = (Real)S.mass;
-    const Real4 vi = vr[i];
-    const Real4 oi = xo[i];
     const uint32_t ci = unpack_index(oi.w);
     const Real rhoi = rho_abs<P>(S, vi.w);
     const Real pi = press<P>(S, vi.w);
     const Real c2 = (Real)2 * rcp(rhoi);   // 2 V_i / m_i
+    const Real cc2 = (Real)(S.c0 * S.c0);
     const Real inv_h = (Real)(1.0 / S.h), kF = (Real)S.kF, csr = (Real)S.cs_r;
     Real ax = 0, ay = 0, az = 0;
     const int lane = i & (WAVE - 1);
     const int64_t slice = i >> 6;
-    {
-      const int n = (int)S.nfc[i];
+    // Vj: the neighbour's volume m / rho_j
+    auto pair = [&](Real rx, Real ry, Real rz, const Real4& vj, Real Vj, bool real = true) {
+      const Real r2 = dot_fma(rx, ry, rz, rx, ry, rz), rs = rsq0(r2);
+      Real Fk = kernel_F(r2, rs, inv_h, kF);
+      Fk = real ? Fk : (Real)0;
+      const Real sp = mom_factor<P>(S, rhoi, pi, -c2, c0, cc2, Vj,
+                                    dot_fma(vi.x - vj.x, vi.y - vj.y, vi.z - vj.z, rx, ry, rz), rs, vj.w, Fk);
+      ax = fma(sp, rx, ax);
+      ay = fma(sp, ry, ay);
+      az = fma(sp, rz, az);
+    };
+    const Real gx = (Real)S.g[0], gy = (Real)S.g[1], gz = (Real)S.g[2];
+    const Real rho0 = (Real)S.rho0, ic02 = (Real)(1.0 / (S.c0 * S.c0)), Vw = (Real)S.vol_w;
+    auto wpair = [&](Real rx, Real ry, Real rz, const Real4& lq, bool real) {
+#pragma clang fp contract(off)
+      const Real r2 = dot_fma(rx, ry, rz, rx, ry, rz);
+      Real Fk = kernel_F(r2, rsq0(r2), inv_h, kF);
+      Fk = real ? Fk : (Real)0;
+      const Real sp = wall_factor(rhoi, pi, c2, Vw, rho0, ic02, dot_fma(gx, gy, gz, rx, ry, rz), Fk);
+      ax = fma(sp, rx, ax);
+      ay = fma(sp, ry, ay);
+      az = fma(sp, rz, az);
+      acc.moment(sp * rx, sp * ry, sp * rz, lq);
+    };
+    wall = nw > 0;
+    if (staged) {
+      if constexpr (CANSTAGE) {
+        staged_row(row_groups(S, i), ef, nn, smem, shift, oi, pair);
+        staged_wall(wall_groups(S, i), ew, nw, smem, shift, [&](const Set4& W, const bool(&real)[4]) {
+          const float w[4] = {W.v[0].w, W.v[1].w, W.v[2].w, W.v[3].w};
+          int b[4];
+          const bool one = acc.current(w, real, b);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (!one && !acc.select(b[u])) raise_flag(S, F_CAPACITY);
+            Real rx, ry, rz;
+            set_vec(W, u, oi, rx, ry, rz);
+            wpair(rx, ry, rz, W.v[u], real[u]);
+          }
+        });
+      }
+    } else {
       const GLB uint32_t* R = gpc<uint32_t>(S.nrec) + slice * (int64_t)S.kf * WAVE + lane;
       uint32_t jn[ROW_UNROLL];
 #pragma unroll
       for (int u = 0; u < ROW_UNROLL; ++u) jn[u] = ldnt(R + (int64_t)u * WAVE);
-      for (int k = 0; k < n; k += ROW_UNROLL) {
+      for (int k = 0; k < nn; k += ROW_UNROLL) {
         uint32_t j[ROW_UNROLL];
 #pragma unroll
-        for (int u = 0; u < ROW_UNROLL; ++u) j[u] = k + u < n ? jn[u] : (uint32_t)i;
+        for (int u = 0; u < ROW_UNROLL; ++u) j[u] = k + u < nn ? jn[u] : (uint32_t)i;
         Real4 vj[ROW_UNROLL], oj[ROW_UNROLL];
 #pragma unroll
         for (int u = 0; u < ROW_UNROLL; ++u) {
           oj[u] = xo[j[u]];
           vj[u] = vr[j[u]];
         }
-        if (k + ROW_UNROLL < n) {
+        if (k + ROW_UNROLL < nn) {
 #pragma unroll
           for (int u = 0; u < ROW_UNROLL; ++u) jn[u] = ldnt(R + (int64_t)(k + ROW_UNROLL + u) * WAVE);
         }
@@ -1466,67 +1918,33 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
         for (int u = 0; u < ROW_UNROLL; ++u) {
           Real rx, ry, rz;
           pair_vec(oi, ci, oj[u], csr, rx, ry, rz);
-          const Real r2 = rx * rx + ry * ry + rz * rz;
-          const Real inv = r2 > (Real)0 ? rsq(r2) : (Real)0;
-          const Real Fk = k + u < n ? kernel_F(r2, inv_h, kF) : (Real)0;
-          const Real rhoj = rho_abs<P>(S, vj[u].w);
-          const Real pj = press<P>(S, vj[u].w);
-          // U_L - U_R = -(v_i - v_j) . e_ij
-          const Real dU = -((vi.x - vj[u].x) * rx + (vi.y - vj[u].y) * ry + (vi.z - vj[u].z) * rz) * inv;
-          const Real beta = fmin((Real)3 * fmax(dU, (Real)0), c0);
-          const Real ps = (Real)0.5 * (pi + pj) + rhoi * rhoj * beta * dU * rcp(rhoi + rhoj);
-          const Real s = -c2 * (m * rcp(rhoj)) * ps * Fk;
-          ax += s * rx;
-          ay += s * ry;
-          az += s * rz;
+          pair(rx, ry, rz, vj[u], m * rcp(rho_abs<P>(S, vj[u].w)), k + u < nn);
         }
       }
-    }
-    {
-      const int n = (int)S.nsc[i];
-      wall = n > 0;
-      const GLB uint32_t* R = gpc<uint32_t>(S.srec) + slice * (int64_t)S.ks * WAVE + lane;
+      R = gpc<uint32_t>(S.srec) + slice * (int64_t)S.ks * WAVE + lane;
       const GLB Real4* so = gpc<Real4>(S.so);
-      const GLB Real4* lv = gpc<Real4>(S.lev);
-      const Real gx = (Real)S.g[0], gy = (Real)S.g[1], gz = (Real)S.g[2];
-      const Real rho0 = (Real)S.rho0;
-      const Real ic02 = (Real)(1.0 / (S.c0 * S.c0));
-      const Real Vw = (Real)S.vol_w;
       uint32_t wn[SOLID_UNROLL];
 #pragma unroll
       for (int u = 0; u < SOLID_UNROLL; ++u) wn[u] = ldnt(R + (int64_t)u * WAVE);
-      for (int k0 = 0; k0 < n; k0 += SOLID_UNROLL) {
+      for (int k0 = 0; k0 < nw; k0 += SOLID_UNROLL) {
         Real4 owu[SOLID_UNROLL], lqu[SOLID_UNROLL];
 #pragma unroll
         for (int u = 0; u < SOLID_UNROLL; ++u) {
-          const uint32_t w = k0 + u < n ? wn[u] : 0u;
+          const uint32_t w = k0 + u < nw ? wn[u] : 0u;
           owu[u] = so[w];
           lqu[u] = lv[w];
         }
-        if (k0 + SOLID_UNROLL < n) {
+        if (k0 + SOLID_UNROLL < nw) {
 #pragma unroll
           for (int u = 0; u < SOLID_UNROLL; ++u) wn[u] = ldnt(R + (int64_t)(k0 + SOLID_UNROLL + u) * WAVE);
         }
 #pragma unroll
         for (int u = 0; u < SOLID_UNROLL; ++u) {
-        if (k0 + u >= n) break;
-        const Real4 ow = owu[u], lq = lqu[u];
-        Real rx, ry, rz;
-        pair_vec(oi, ci, ow, csr, rx, ry, rz);
-        const Real Fk = kernel_F(rx * rx + ry * ry + rz * rz, inv_h, kF);
-        // right state of eq. 17: P_R = P_L + rho_f g . (x_w - x_f), rho_R from the EoS
-        const Real PR = pi - rhoi * (gx * rx + gy * ry + gz * rz);
-        const Real rhoR = rho0 + PR * ic02;
-        const Real ps = (rhoi * PR + rhoR * pi) * rcp(rhoi + rhoR);   // eq. 19
-        const Real s = -c2 * Vw * ps * Fk;
-        const Real fx = s * rx, fy = s * ry, fz = s * rz;
-        ax += fx;
-        ay += fy;
-        az += fz;
-        const double hx = -(double)m * fx, hy = -(double)m * fy, hz = -(double)m * fz;
-        const double lx = lq.x, ly = lq.y, lz = lq.z;
-        const double contrib[6] = {hx, hy, hz, ly * hz - lz * hy, lz * hx - lx * hz, lx * hy - ly * hx};
-        if (!acc.add((int)lq.w, contrib)) raise_flag(S, F_CAPACITY);
+          if (k0 + u >= nw) break;
+          Real rx, ry, rz;
+          pair_vec(oi, ci, owu[u], csr, rx, ry, rz);
+          if (!acc.select((int)lqu[u].w)) raise_flag(S, F_CAPACITY);
+          wpair(rx, ry, rz, lqu[u], true);
         }
       }
     }
@@ -1546,6 +1964,7 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
     d.z += hdt * vn.z;
     dr[i] = d;
   }
+  acc.to_force((double)(Real)S.mass);
   if (__syncthreads_or(wall))
     block_body_reduce<6>(acc, S.nbody, S.press_part, (size_t)S.nblk[DOM_FLUID], lb, true, lds);
 }
@@ -1559,99 +1978,131 @@ template <class P>
 __global__ __launch_bounds__(BLOCK) void k_continuity(const SlotDesc* table, LaunchTab tab, int sub) {
   typedef typename P::Real Real;
   typedef typename P::Real4 Real4;
-  SLOT_PROLOGUE(DOM_FLUID);
-  if (sub >= S.ctl->n_ac) return;
+  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
+  __shared__ __attribute__((aligned(32))) char smem[CANSTAGE ? STAGE_CAP * 32 : 32];
+  __shared__ float shift[CANSTAGE ? 3 * SHIFT_LD : 1];
+  SLOT_FIND(DOM_FLUID);
   const int i = lb * BLOCK + threadIdx.x;
-  if (i >= S.nf) return;
+  const int ii = min(i, S.nf - 1);
   const GLB Real4* vrn = gpc<Real4>(S.vrn);
   const GLB Real4* xo = gpc<Real4>(S.xo);
+  const GLB Real4* nuw = gpc<Real4>(S.nuw);
+  BlkHead hd;
+  StageList sl;
+  if constexpr (CANSTAGE) {
+    hd = blk_head(S, lb);
+    sl = stage_list(S, lb);
+  }
+  const Real4 vi = vrn[ii];
+  const Real4 oi = xo[ii];
+  const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
+  if (!live_sub(S, sub)) return;
+  const bool staged = CANSTAGE && hd.n >= 0;
+  Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
+  if constexpr (CANSTAGE) {
+    if (staged) {
+      ef = row_load(row_groups(S, ii), 0);
+      ew = row_load(wall_groups(S, ii), 0);
+      stage_pairs<P>(S, hd, sl, vrn, nuw, smem, shift);
+      __syncthreads();
+    }
+  }
+  if (i >= S.nf) return;
   const Real c0 = (Real)S.c0;
   const Real m = (Real)S.mass;
-  const Real4 vi = vrn[i];
-  const Real4 oi = xo[i];
   const uint32_t ci = unpack_index(oi.w);
   const Real rhoi = rho_abs<P>(S, vi.w);
   const Real pi = press<P>(S, vi.w);
   const Real inv_h = (Real)(1.0 / S.h), kF = (Real)S.kF, csr = (Real)S.cs_r;
+  const Real cc2 = (Real)(S.c0 * S.c0);
   Real sum = 0;
   const int lane = i & (WAVE - 1);
   const int64_t slice = i >> 6;
-  {
-    const int n = (int)S.nfc[i];
+  // Vj: the neighbour's volume m / rho_j
+  auto pair = [&](Real rx, Real ry, Real rz, const Real4& vj, Real Vj, bool real = true) {
+    const Real r2 = dot_fma(rx, ry, rz, rx, ry, rz), rs = rsq0(r2);
+    Real Fk = kernel_F(r2, rs, inv_h, kF);
+    Fk = real ? Fk : (Real)0;
+    sum = fma(cont_factor<P>(S, rhoi, pi, c0, cc2, Vj, dot_fma(vi.x - vj.x, vi.y - vj.y, vi.z - vj.z, rx, ry, rz),
+                             r2 * rs, vj.w),
+              Fk, sum);
+  };
+  const Real gx = (Real)S.g[0], gy = (Real)S.g[1], gz = (Real)S.g[2];
+  const Real rho0 = (Real)S.rho0, ic02 = (Real)(1.0 / (S.c0 * S.c0)), Vw = (Real)S.vol_w;
+  // nq: the wall normal and u_w = -n . v_w
+  auto wpair = [&](Real rx, Real ry, Real rz, const Real4& nq, bool real) {
+#pragma clang fp contract(off)
+    const Real r2 = dot_fma(rx, ry, rz, rx, ry, rz);
+    Real Fk = kernel_F(r2, rsq0(r2), inv_h, kF);
+    Fk = real ? Fk : (Real)0;
+    const Real PR = fma(-rhoi, dot_fma(gx, gy, gz, rx, ry, rz), pi);
+    const Real rhoR = fma(PR, ic02, rho0);
+    const Real UL = -dot_fma(nq.x, nq.y, nq.z, vi.x, vi.y, vi.z);
+    const Real Us = fma(pi - PR, rcp(c0 * (rhoi + rhoR)), nq.w);
+    sum = fma(Vw * (Us - UL) * dot_fma(nq.x, nq.y, nq.z, rx, ry, rz), Fk, sum);
+  };
+  if (staged) {
+    if constexpr (CANSTAGE) {
+      staged_row(row_groups(S, i), ef, nn, smem, shift, oi, pair);
+      staged_wall(wall_groups(S, i), ew, nw, smem, shift, [&](const Set4& W, const bool(&real)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          Real rx, ry, rz;
+          set_vec(W, u, oi, rx, ry, rz);
+          wpair(rx, ry, rz, W.v[u], real[u]);
+        }
+      });
+    }
+  } else {
+    constexpr int U = CANSTAGE ? CONT_UNROLL : ROW_UNROLL;
     const GLB uint32_t* R = gpc<uint32_t>(S.nrec) + slice * (int64_t)S.kf * WAVE + lane;
-    uint32_t jn[CONT_UNROLL];
+    uint32_t jn[U];
 #pragma unroll
-    for (int u = 0; u < CONT_UNROLL; ++u) jn[u] = ldnt(R + (int64_t)u * WAVE);
-    for (int k = 0; k < n; k += CONT_UNROLL) {
-      uint32_t j[CONT_UNROLL];
+    for (int u = 0; u < U; ++u) jn[u] = ldnt(R + (int64_t)u * WAVE);
+    for (int k = 0; k < nn; k += U) {
+      uint32_t j[U];
 #pragma unroll
-      for (int u = 0; u < CONT_UNROLL; ++u) j[u] = k + u < n ? jn[u] : (uint32_t)i;
-      Real4 vj[CONT_UNROLL], oj[CONT_UNROLL];
+      for (int u = 0; u < U; ++u) j[u] = k + u < nn ? jn[u] : (uint32_t)i;
+      Real4 vj[U], oj[U];
 #pragma unroll
-      for (int u = 0; u < CONT_UNROLL; ++u) {
+      for (int u = 0; u < U; ++u) {
         oj[u] = xo[j[u]];
         vj[u] = vrn[j[u]];
       }
-      if (k + CONT_UNROLL < n) {
+      if (k + U < nn) {
 #pragma unroll
-        for (int u = 0; u < CONT_UNROLL; ++u)
-          jn[u] = ldnt(R + (int64_t)min(k + CONT_UNROLL + u, S.kf - 1) * WAVE);
+        for (int u = 0; u < U; ++u) jn[u] = ldnt(R + (int64_t)min(k + U + u, S.kf - 1) * WAVE);
       }
 #pragma unroll
-      for (int u = 0; u < CONT_UNROLL; ++u) {
+      for (int u = 0; u < U; ++u) {
         Real rx, ry, rz;
         pair_vec(oi, ci, oj[u], csr, rx, ry, rz);
-        const Real r2 = rx * rx + ry * ry + rz * rz;
-        const Real rr = r2 > (Real)0 ? r2 * rsq(r2) : (Real)0;
-        const Real Fk = k + u < n ? kernel_F(r2, inv_h, kF) : (Real)0;
-        const Real rhoj = rho_abs<P>(S, vj[u].w);
-        const Real pj = press<P>(S, vj[u].w);
-        // (U* - U_L) dW = [ (v_i - v_j) . r / 2 + (p_i - p_j) r / (c0 (rho_i + rho_j)) ] F
-        const Real vr_ = (vi.x - vj[u].x) * rx + (vi.y - vj[u].y) * ry + (vi.z - vj[u].z) * rz;
-        const Real dv = (Real)0.5 * vr_ + (pi - pj) * rr * rcp(c0 * (rhoi + rhoj));
-        sum += (m * rcp(rhoj)) * dv * Fk;
+        pair(rx, ry, rz, vj[u], m * rcp(rho_abs<P>(S, vj[u].w)), k + u < nn);
       }
     }
-  }
-  {
-    const int n = (int)S.nsc[i];
-    const GLB uint32_t* R = gpc<uint32_t>(S.srec) + slice * (int64_t)S.ks * WAVE + lane;
+    R = gpc<uint32_t>(S.srec) + slice * (int64_t)S.ks * WAVE + lane;
     const GLB Real4* so = gpc<Real4>(S.so);
-    const GLB Real4* nw = gpc<Real4>(S.nw);
-    const GLB Real4* vw = gpc<Real4>(S.vw);
-    const Real gx = (Real)S.g[0], gy = (Real)S.g[1], gz = (Real)S.g[2];
-    const Real rho0 = (Real)S.rho0;
-    const Real ic02 = (Real)(1.0 / (S.c0 * S.c0));
-    const Real Vw = (Real)S.vol_w;
     uint32_t wn[SOLID_UNROLL];
 #pragma unroll
     for (int u = 0; u < SOLID_UNROLL; ++u) wn[u] = ldnt(R + (int64_t)u * WAVE);
-    for (int k0 = 0; k0 < n; k0 += SOLID_UNROLL) {
-      Real4 owu[SOLID_UNROLL], nqu[SOLID_UNROLL], vqu[SOLID_UNROLL];
+    for (int k0 = 0; k0 < nw; k0 += SOLID_UNROLL) {
+      Real4 owu[SOLID_UNROLL], nqu[SOLID_UNROLL];
 #pragma unroll
       for (int u = 0; u < SOLID_UNROLL; ++u) {
-        const uint32_t w = k0 + u < n ? wn[u] : 0u;
+        const uint32_t w = k0 + u < nw ? wn[u] : 0u;
         owu[u] = so[w];
-        nqu[u] = nw[w];
-        vqu[u] = vw[w];
+        nqu[u] = nuw[w];
       }
-      if (k0 + SOLID_UNROLL < n) {
+      if (k0 + SOLID_UNROLL < nw) {
 #pragma unroll
         for (int u = 0; u < SOLID_UNROLL; ++u) wn[u] = ldnt(R + (int64_t)(k0 + SOLID_UNROLL + u) * WAVE);
       }
 #pragma unroll
       for (int u = 0; u < SOLID_UNROLL; ++u) {
-      if (k0 + u >= n) break;
-      const Real4 ow = owu[u], nq = nqu[u], vq = vqu[u];
-      Real rx, ry, rz;
-      pair_vec(oi, ci, ow, csr, rx, ry, rz);
-      const Real Fk = kernel_F(rx * rx + ry * ry + rz * rz, inv_h, kF);
-      const Real PR = pi - rhoi * (gx * rx + gy * ry + gz * rz);
-      const Real rhoR = rho0 + PR * ic02;
-      const Real UL = -(nq.x * vi.x + nq.y * vi.y + nq.z * vi.z);
-      const Real uw = -(nq.x * vq.x + nq.y * vq.y + nq.z * vq.z);
-      const Real Us = uw + (pi - PR) * rcp(c0 * (rhoi + rhoR));
-      sum += Vw * (Us - UL) * (nq.x * rx + nq.y * ry + nq.z * rz) * Fk;
+        if (k0 + u >= nw) break;
+        Real rx, ry, rz;
+        pair_vec(oi, ci, owu[u], csr, rx, ry, rz);
+        wpair(rx, ry, rz, nqu[u], true);
       }
     }
   }

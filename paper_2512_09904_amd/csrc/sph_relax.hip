@@ -204,6 +204,13 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
   const SlotDesc& S = table[tab.slot[sk]];
   if (!live(S)) return;
   ls_flank_table(g, E);
+  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
+  bool staged = false;
+  const GLB uint32_t* list = nullptr;
+  if constexpr (CANSTAGE) {
+    staged = blk_head(S, lb).n >= 0;
+    list = gpc<uint32_t>(S.blist) + (int64_t)lb * STAGE_CAP;
+  }
   __syncthreads();
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   const int i = lb * BLOCK + quarter * WAVE + lane;
@@ -223,10 +230,14 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
     const int n = (int)S.nfc[i];
     const GLB uint32_t* R = gpc<uint32_t>(S.nrec) + (int64_t)(i >> 6) * S.kf * WAVE + lane;
     for (int k = 0; k < n; ++k) {
-      const uint32_t j = ldnt(R + (int64_t)k * WAVE);
+      // a staged row's entry names the particle in the block's list
+      const uint32_t e = staged ? ((const GLB uint32_t*)(row_groups(S, i) + (int64_t)(k >> 2) * WAVE))[k & 3]
+                                : ldnt(R + (int64_t)k * WAVE);
+      const uint32_t j = staged ? list[(e & 0xffffu) >> 4] : e;
       Real rx, ry, rz;
       pair_vec(oi, ci, xo[j], csr, rx, ry, rz);
-      const Real Fk = kernel_F(rx * rx + ry * ry + rz * rz, inv_h, kF);
+      const Real r2 = rx * rx + ry * ry + rz * rz;
+      const Real Fk = kernel_F(r2, rsq0(r2), inv_h, kF);
       ax += Fk * rx;
       ay += Fk * ry;
       az += Fk * rz;
