@@ -1412,7 +1412,7 @@ extern "C" int sph_debug_dump(sph_solver* s, int32_t what, void* buf, size_t byt
       uint32_t* o = (uint32_t*)buf;
       unsell(pl, K, [&](size_t i, int k, size_t src) { o[i * (size_t)K + (size_t)k] = r[src]; });
       if (pl.prec == SPH_PREC_FP64) return SPH_OK;
-      // blocks with staged candidates hold local indices, [slice][k / 4][lane]
+      // staged wavefronts' rows hold local indices, [slice][k / 4][lane]
       // in groups of four entries; back to sorted indices by the block's list
       const size_t nb = (size_t)pl.nblk[DOM_FLUID];
       std::vector<BlkHead> hd(nb);
@@ -1421,7 +1421,7 @@ extern "C" int sph_debug_dump(sph_solver* s, int32_t what, void* buf, size_t byt
       LCHK(d2h(list.data(), D.blist, list.size() * 4));
       LCHK(d2h(cnt.data(), sol ? D.nsc : D.nfc, nf * 4));
       for (size_t i = 0; i < nf; ++i) {
-        if (hd[i / BLOCK].n < 0) continue;
+        if (!(hd[i / BLOCK].waves >> (i % BLOCK / WAVE) & 1)) continue;
         const uint32_t* row = r.data() + (i / WAVE) * (size_t)K * WAVE;
         const uint32_t* glob = list.data() + (i / BLOCK) * STAGE_CAP;
         for (size_t k = 0; k < (size_t)K; ++k)

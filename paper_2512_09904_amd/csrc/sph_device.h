@@ -349,7 +349,12 @@ __device__ __forceinline__ BlkHead blk_head(const SlotDesc& S, int lb) {
   return __builtin_bit_cast(BlkHead, (u4)gpc<u4>(S.bhead)[lb]);
 }
 
-// This thread's candidates t, t + BLOCK, ... of the block's list.  Loaded whole,
+// whether wavefront w's rows hold local indices
+__device__ __forceinline__ bool wave_staged(const BlkHead& hd, int w) { return (hd.waves >> w) & 1; }
+// this wavefront's index in the block, as a scalar
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x) / WAVE; }
+
+// This thread's candidates t, t + BLOCK, ... of a part's list.  Loaded whole,
 // before the block's head is known (entries past the candidates are never
 // used): a sweep's first wait covers the head, the list and its own records.
 constexpr int STAGE_U = (STAGE_CAP + BLOCK - 1) / BLOCK;
@@ -365,13 +370,13 @@ __device__ __forceinline__ StageList stage_list(const SlotDesc& S, int lb) {
 }
 
 // store(l, load(solid or not, j), j) for every candidate l of the block, j its
-// sorted index.  The solids start at a multiple of the wavefront, so the source
-// is the same for a wavefront's lanes.  There is no branch between the loads
-// (lanes past the candidates take particle 0 and store nothing): with one, each
-// load would wait for the one before.  Half of a thread's records are in flight
-// together.
+// sorted index, and the barrier.  The solids start at a multiple of the
+// wavefront, so the source is the same for a wavefront's lanes.  There is no
+// branch between the loads (lanes past the candidates take particle 0 and store
+// nothing): with one, each load would wait for the one before.  Half of a
+// thread's records are in flight together.
 template <class Load, class Store>
-__device__ __forceinline__ void stage_candidates(const BlkHead& hd, const StageList& sl, Load&& load, Store&& store) {
+__device__ __forceinline__ void stage_block(const BlkHead& hd, const StageList& sl, Load&& load, Store&& store) {
   constexpr int U = STAGE_U, H = U / 2;
 #pragma unroll
   for (int h = 0; h < U; h += H) {
@@ -389,6 +394,7 @@ __device__ __forceinline__ void stage_candidates(const BlkHead& hd, const StageL
       if (l < hd.n) store((uint32_t)l, r[u], j[u]);
     }
   }
+  __syncthreads();
 }
 
 // Shift of a neighbour's cell-relative position into the particle's cell, by

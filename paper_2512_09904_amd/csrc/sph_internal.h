@@ -33,17 +33,20 @@ struct LaunchTab {
 // Neighbour candidates of one fluid block (BLOCK consecutive sorted
 // particles): the fluid, then the solid particles of the cells in the 27-cell
 // stencils of the block's particles, each cell once, numbered 0..n-1 ("local
-// index", the solids from a multiple of 64 on).  With n >= 0 the FP32 sweeps
-// stage the candidates' records in LDS and the block's rows hold
+// index", the solids from a multiple of 64 on).  The FP32 sweeps stage the
+// candidates' records in LDS and the block's rows hold
 //   16 * (local index) | 4 * (stencil cell 0..26) << 16
-// in groups of four; with n < 0 the rows hold sorted indices and the sweeps
-// gather from memory.  FP64 mode has neither heads nor lists: its rows always
-// hold sorted indices.
+// in groups of four.  A block that straddles a jump of the Morton order has
+// more candidates than fit (one in ten): three of its wavefronts are staged, the
+// rows of the other hold sorted indices and its lanes gather from memory.  If
+// that does not fit either (one block in a thousand), all four gather.
+// FP64 mode has neither heads nor lists: its rows always hold sorted indices.
 constexpr int STAGE_CAP = 2432;      // 32 B per candidate: two blocks' worth fit the CU's 160 KB
 struct BlkHead {
-  int32_t n;
+  int32_t n;                         // candidates (0: none staged)
   int32_t ns0;                       // local index of the first solid particle
-  int32_t pad[2];
+  int32_t waves;                     // bit w: wavefront w's rows hold local indices
+  int32_t pad;
 };
 constexpr int STAGE_ITEMS = 256;     // cells per block and set (at most 255 used)
 // One cell of a block's candidates: sorted particles [start, start + cnt) have

@@ -646,17 +646,18 @@ struct StageTab {
   uint16_t id[2][27 * MAXRUN];       // the entry's item: fluid, solid
   BlkItem item[2][STAGE_ITEMS];
   uint32_t scan[BLOCK / WAVE], last[BLOCK / WAVE];
+  int cont1;                         // wavefront 1 starts within a run
 };
 
-// Fills the table and writes the block's head and list; returns whether the
-// block's candidates fit.  nruns <= MAXRUN.
-__device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb, int lb, int nruns) {
+// Fills the table for the runs [r0, r1) and writes the block's head, with the
+// given wavefronts staged, and list; returns whether the candidates fit.
+__device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb, int lb, int r0, int r1, int waves) {
   const GLB uint32_t* rank = gpc<uint32_t>(S.rank);
   const GLB uint32_t* st[2] = {gpc<uint32_t>(S.start_f), gpc<uint32_t>(S.start_s)};
-  const int n = 27 * nruns;
+  const int n = 27 * r1;
   uint32_t done[2] = {0u, 0u};       // (cells << 21) | candidates numbered so far
   bool big = false;
-  for (int i0 = 0; i0 < n; i0 += BLOCK) {
+  for (int i0 = 27 * r0; i0 < n; i0 += BLOCK) {
     const int it = i0 + (int)threadIdx.x;
     uint32_t f0[2] = {0u, 0u}, cnt[2] = {0u, 0u};
     int ref = -1;
@@ -666,7 +667,7 @@ __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb
       const int x = (int)(hc & 1023u) + q % 3 - 1, y = (int)((hc >> 10) & 1023u) + (q / 3) % 3 - 1,
                 z = (int)(hc >> 20) + q / 9 - 1;
       if (x >= 0 && y >= 0 && z >= 0 && x < S.dims[0] && y < S.dims[1] && z < S.dims[2]) {
-        for (int p = 0; p < r; ++p) {
+        for (int p = r0; p < r; ++p) {
           const uint32_t h = tb.home[p];
           const uint32_t dx = (uint32_t)(x - (int)(h & 1023u) + 1), dy = (uint32_t)(y - (int)((h >> 10) & 1023u) + 1),
                          dz = (uint32_t)(z - (int)(h >> 20) + 1);
@@ -703,14 +704,14 @@ __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb
   const int ni[2] = {(int)(done[0] >> 21), (int)(done[1] >> 21)};
   const int ns0 = (nc[0] + WAVE - 1) / WAVE * WAVE, nt = ns0 + nc[1];
   const bool ok = !__syncthreads_or(big) && nt <= STAGE_CAP && ni[0] < STAGE_ITEMS && ni[1] < STAGE_ITEMS;
-  if (threadIdx.x == 0) S.bhead[lb] = BlkHead{ok ? nt : -1, ns0, {0, 0}};
   if (!ok) return false;
+  if (threadIdx.x == 0) S.bhead[lb] = BlkHead{nt, ns0, waves, 0};
   uint32_t* list = S.blist + (int64_t)lb * STAGE_CAP;
   if (nc[0] + (int)threadIdx.x < ns0) list[nc[0] + threadIdx.x] = 0u;
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
     if (a && (int)threadIdx.x < ni[1]) tb.item[1][threadIdx.x].base += (uint16_t)ns0;
-    for (int it = threadIdx.x; it < n; it += BLOCK) {
+    for (int it = 27 * r0 + threadIdx.x; it < n; it += BLOCK) {
       const uint16_t v = tb.id[a][it];
       if (v != NO_ITEM && (v & ITEM_REF)) tb.id[a][it] = tb.id[a][v & 0x7fffu];
     }
@@ -765,20 +766,27 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
     const bool cont = wv > 0 && tb.last[wv > 0 ? wv - 1 : 0] == (uint32_t)__builtin_amdgcn_readlane((int)pc, 0);
     const uint64_t heads = cont ? runs & ~1ull : runs;
     if (lane == 0) tb.scan[wv] = (uint32_t)__popcll(heads);
+    if (threadIdx.x == WAVE) tb.cont1 = cont;
     __syncthreads();
-    int nruns = 0;
+    int nruns = 0, cut1 = 0, cut3 = 0;   // runs that start in wavefront 0, in 0 to 2
     for (int w = 0; w < BLOCK / WAVE; ++w) {
+      if (w == 1) cut1 = nruns;
+      if (w == 3) cut3 = nruns;
       if (w < wv) run += (int)tb.scan[w];
       nruns += (int)tb.scan[w];
     }
     run += __popcll(heads & (lane == WAVE - 1 ? ~0ull : (2ull << lane) - 1)) - 1;
+    int waves = 0;
     if (nruns <= MAXRUN) {
       if ((heads >> lane) & 1) tb.home[run] = pc;
       __syncthreads();
-      staged = block_candidates(S, tb, lb, nruns);
-    } else if (threadIdx.x == 0) {
-      S.bhead[lb] = BlkHead{-1, 0, {0, 0}};
+      // all four wavefronts, or the first or the last three
+      if (block_candidates(S, tb, lb, 0, nruns, 15)) waves = 15;
+      else if (block_candidates(S, tb, lb, 0, cut3, 7)) waves = 7;
+      else if (block_candidates(S, tb, lb, cut1 - tb.cont1, nruns, 14)) waves = 14;
     }
+    if (waves == 0 && threadIdx.x == 0) S.bhead[lb] = BlkHead{0, 0, 0, 0};
+    staged = (waves >> wv) & 1;
   }
   GLB uint32_t* rows = gp<uint32_t>(S.rmaj);
   const GLB uint32_t* rank = gpc<uint32_t>(S.rank);
@@ -931,15 +939,18 @@ __global__ __launch_bounds__(BLOCK) void k_sumw(const SlotDesc* table, LaunchTab
   const Pos4 xi4 = xa[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
   if (!live(S)) return;
-  const bool staged = CANSTAGE && hd.n >= 0;
+  const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   Pos4* wxa = (Pos4*)smem;
-  const Window win = window_of(lb, S.nf);
+  const bool block_gathers = !CANSTAGE || hd.n == 0;
+  const Window win = block_gathers ? window_of(lb, S.nf) : Window{0, 0};
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
   if constexpr (CANSTAGE) {
-    if (staged) {
-      ef = row_load(row_groups(S, ii), 0);
-      ew = row_load(wall_groups(S, ii), 0);
-      stage_candidates(
+    if (hd.n > 0) {
+      if (staged) {
+        ef = row_load(row_groups(S, ii), 0);
+        ew = row_load(wall_groups(S, ii), 0);
+      }
+      stage_block(
           hd, sl, [&](bool sol, uint32_t j) { return (sol ? xw : xa)[j]; },
           [&](uint32_t l, const Pos4& x, uint32_t) {
             if constexpr (sizeof(Pos) == 8) {
@@ -953,8 +964,10 @@ __global__ __launch_bounds__(BLOCK) void k_sumw(const SlotDesc* table, LaunchTab
           });
     }
   }
-  if (!staged) stage_window(wxa, xa, win);
-  __syncthreads();
+  if (block_gathers) {
+    stage_window(wxa, xa, win);
+    __syncthreads();
+  }
   if (i >= S.nf) return;
   const Pos xi = xi4.x, yi = xi4.y, zi = xi4.z;
   const double inv_h = 1.0 / S.h, kW = S.kW;
@@ -1419,28 +1432,8 @@ __global__ __launch_bounds__(BLOCK)
   const Real drhoi = gpc<Real>(S.drho)[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
   if (!live(S)) return;
-  const bool staged = CANSTAGE && hd.n >= 0;
+  const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   const bool mats = MAT && S.mat != nullptr;
-  Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
-  if constexpr (CANSTAGE) {
-    if (staged) {
-      ef = row_load(row_groups(S, ii), 0);
-      ew = row_load(wall_groups(S, ii), 0);
-      shift_table(shift, (float)S.cs_r);
-      const GLB f4* so = gpc<f4>(S.so);
-      const GLB f4* vdb = gpc<f4>(S.vdb);
-      // the position record's fourth word takes the sorted index, at which the
-      // temperature record or the lever arm is gathered
-      stage_candidates(
-          hd, sl, [&](bool sol, uint32_t j) { return RecPair{(sol ? so : xo)[j], (sol ? vdb : vr)[j]}; },
-          [&](uint32_t l, const RecPair& r, uint32_t j) {
-            f4 o = r.a;
-            o.w = pack_index(j, 0.0f);
-            *(f4*)(smem + 16 * l) = o;
-            *(f4*)(smem + 16 * l + 16 * STAGE_CAP) = r.b;
-          });
-    }
-  }
   if (mats) {
     for (int q = threadIdx.x; q < NMAT * NMAT; q += BLOCK) {
       const double ka = S.mk[q / NMAT], kb = S.mk[q % NMAT];
@@ -1453,7 +1446,29 @@ __global__ __launch_bounds__(BLOCK)
     Kwall[mq * NB + b] = (Real)(4.0 * k * S.bk[b] / (k + S.bk[b]));
     if (mq == 0) Tb[b] = (Temp)S.bT[b];
   }
-  __syncthreads();
+  Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
+  if constexpr (CANSTAGE) {
+    if (hd.n > 0) {
+      if (staged) {
+        ef = row_load(row_groups(S, ii), 0);
+        ew = row_load(wall_groups(S, ii), 0);
+      }
+      shift_table(shift, (float)S.cs_r);
+      const GLB f4* so = gpc<f4>(S.so);
+      const GLB f4* vdb = gpc<f4>(S.vdb);
+      // the position record's fourth word takes the sorted index, at which the
+      // temperature record or the lever arm is gathered
+      stage_block(
+          hd, sl, [&](bool sol, uint32_t j) { return RecPair{(sol ? so : xo)[j], (sol ? vdb : vr)[j]}; },
+          [&](uint32_t l, const RecPair& r, uint32_t j) {
+            f4 o = r.a;
+            o.w = pack_index(j, 0.0f);
+            *(f4*)(smem + 16 * l) = o;
+            *(f4*)(smem + 16 * l + 16 * STAGE_CAP) = r.b;
+          });
+    }
+  }
+  if (!CANSTAGE || hd.n == 0) __syncthreads();
   const size_t nbf = (size_t)S.nblk[DOM_FLUID];
   if (threadIdx.x < NB * 6) S.press_part[(size_t)threadIdx.x * nbf + lb] = 0.0;
   BodyAcc<7> acc;
@@ -1779,15 +1794,15 @@ __global__ __launch_bounds__(BLOCK) void k_half_a(const SlotDesc* table, LaunchT
 // Stages the candidates of a momentum or continuity sweep: cell-relative
 // positions with the particle's volume m / rho as the fourth component, then
 // the records b (fluid: velocity and density) and ws (solid) at 16 * STAGE_CAP,
-// and the shift table.  The caller synchronises.
+// and the shift table.
 template <class P>
-__device__ __forceinline__ void stage_pairs(const SlotDesc& S, const BlkHead& hd, const StageList& sl, const GLB f4* b,
-                                            const GLB f4* ws, char* smem, float* shift) {
+__device__ __forceinline__ void stage_pairs(const SlotDesc& S, const BlkHead& hd, const StageList& sl,
+                                            const GLB f4* b, const GLB f4* ws, char* smem, float* shift) {
   const GLB f4* xo = gpc<f4>(S.xo);
   const GLB f4* so = gpc<f4>(S.so);
   const float m = (float)S.mass;
   shift_table(shift, (float)S.cs_r);
-  stage_candidates(
+  stage_block(
       hd, sl, [&](bool sol, uint32_t j) { return RecPair{(sol ? so : xo)[j], (sol ? ws : b)[j]}; },
       [&](uint32_t l, const RecPair& r, uint32_t) {
         f4 o = r.a;
@@ -1829,14 +1844,15 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
   const Real4 oi = xo[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
   if (!live_sub(S, sub)) return;
-  const bool staged = CANSTAGE && hd.n >= 0;
+  const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
   if constexpr (CANSTAGE) {
-    if (staged) {
-      ef = row_load(row_groups(S, ii), 0);
-      ew = row_load(wall_groups(S, ii), 0);
+    if (hd.n > 0) {
+      if (staged) {
+        ef = row_load(row_groups(S, ii), 0);
+        ew = row_load(wall_groups(S, ii), 0);
+      }
       stage_pairs<P>(S, hd, sl, vr, lv, smem, shift);
-      __syncthreads();
     }
   }
   BodyAcc<6> acc;
@@ -1997,14 +2013,15 @@ __global__ __launch_bounds__(BLOCK) void k_continuity(const SlotDesc* table, Lau
   const Real4 oi = xo[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
   if (!live_sub(S, sub)) return;
-  const bool staged = CANSTAGE && hd.n >= 0;
+  const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
   if constexpr (CANSTAGE) {
-    if (staged) {
-      ef = row_load(row_groups(S, ii), 0);
-      ew = row_load(wall_groups(S, ii), 0);
+    if (hd.n > 0) {
+      if (staged) {
+        ef = row_load(row_groups(S, ii), 0);
+        ew = row_load(wall_groups(S, ii), 0);
+      }
       stage_pairs<P>(S, hd, sl, vrn, nuw, smem, shift);
-      __syncthreads();
     }
   }
   if (i >= S.nf) return;
@@ -2052,7 +2069,7 @@ __global__ __launch_bounds__(BLOCK) void k_continuity(const SlotDesc* table, Lau
           wpair(rx, ry, rz, W.v[u], real[u]);
         }
       });
-    }
+      }
   } else {
     constexpr int U = CANSTAGE ? CONT_UNROLL : ROW_UNROLL;
     const GLB uint32_t* R = gpc<uint32_t>(S.nrec) + slice * (int64_t)S.kf * WAVE + lane;

@@ -208,7 +208,7 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
   bool staged = false;
   const GLB uint32_t* list = nullptr;
   if constexpr (CANSTAGE) {
-    staged = blk_head(S, lb).n >= 0;
+    staged = wave_staged(blk_head(S, lb), quarter);
     list = gpc<uint32_t>(S.blist) + (int64_t)lb * STAGE_CAP;
   }
   __syncthreads();
