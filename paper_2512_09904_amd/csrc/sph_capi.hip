@@ -8,7 +8,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -222,33 +224,31 @@ static size_t carve(const Plan& P, void* base, SlotDesc* d) {
   return (C.off + 255) & ~(size_t)255;
 }
 
-static uint32_t morton3(uint32_t cx, uint32_t cy, uint32_t cz) {
-  uint32_t k = 0;
-  for (int b = 0; b < 10; ++b) {
-    k |= ((cx >> b) & 1u) << (3 * b);
-    k |= ((cy >> b) & 1u) << (3 * b + 1);
-    k |= ((cz >> b) & 1u) << (3 * b + 2);
+// rank of each cell (row-major linear index) in Morton order, and its inverse:
+// the octree's octants in order, those outside the grid left out
+struct RankWalk {
+  const int32_t* dims;
+  uint32_t *rank, *code;
+  uint32_t next = 0;
+  void octant(int32_t x, int32_t y, int32_t z, int level, uint32_t m) {
+    if (x >= dims[0] || y >= dims[1] || z >= dims[2]) return;
+    if (level == 0) {
+      code[next] = m;
+      rank[((int64_t)z * dims[1] + y) * dims[0] + x] = next++;
+      return;
+    }
+    const int32_t e = 1 << (level - 1);
+    for (int32_t k = 0; k < 8; ++k)
+      octant(x + (k & 1 ? e : 0), y + (k & 2 ? e : 0), z + (k & 4 ? e : 0), level - 1,
+             m | (uint32_t)k << 3 * (level - 1));
   }
-  return k;
-}
-
-// rank of each cell (row-major linear index) in Morton order, and its inverse
+};
 static void rank_table(const int32_t dims[3], std::vector<uint32_t>& rank, std::vector<uint32_t>& morton_of_rank) {
-  const int64_t n = (int64_t)dims[0] * dims[1] * dims[2];
-  std::vector<uint64_t> key((size_t)n);
-  for (int32_t z = 0; z < dims[2]; ++z)
-    for (int32_t y = 0; y < dims[1]; ++y)
-      for (int32_t x = 0; x < dims[0]; ++x) {
-        const int64_t lin = ((int64_t)z * dims[1] + y) * dims[0] + x;
-        key[(size_t)lin] = ((uint64_t)morton3((uint32_t)x, (uint32_t)y, (uint32_t)z) << 32) | (uint64_t)lin;
-      }
-  std::sort(key.begin(), key.end());
-  rank.assign((size_t)n, 0u);
-  morton_of_rank.assign((size_t)n, 0u);
-  for (int64_t r = 0; r < n; ++r) {
-    rank[(size_t)(key[(size_t)r] & 0xffffffffu)] = (uint32_t)r;
-    morton_of_rank[(size_t)r] = (uint32_t)(key[(size_t)r] >> 32);
-  }
+  const size_t n = (size_t)dims[0] * dims[1] * dims[2];
+  rank.resize(n);
+  morton_of_rank.resize(n);
+  RankWalk w{dims, rank.data(), morton_of_rank.data()};
+  w.octant(0, 0, 0, 10, 0u);
 }
 
 // perfect-lattice kernel sum dp^3 sum W (self included), the reference of eq. 14
@@ -321,7 +321,7 @@ struct SlotHost {
   std::vector<uint32_t> morton_of_rank;
   // host sources of the slot's stream-ordered uploads: they must outlive the
   // copies, so neither is resized or reassigned while the slot is admitted
-  std::vector<char> staging;
+  std::unique_ptr<char[]> staging;
   SlotCtl ctl_staged{};
 };
 
@@ -623,11 +623,6 @@ extern "C" int sph_pool_create(size_t budget, int32_t max_slots, int32_t precisi
   return SPH_OK;
 }
 
-template <class T>
-static void put(std::vector<char>& buf, size_t off, T val) {
-  std::memcpy(buf.data() + off, &val, sizeof(T));
-}
-
 // host copies converted to the device layout of a slot
 static int upload_slot(sph_pool* P, SlotHost& S, const double* x, const double* v, const double* rho,
                        const double* T, const int32_t* material, const double* x0, const double* n0,
@@ -639,51 +634,65 @@ static int upload_slot(sph_pool* P, SlotHost& S, const double* x, const double* 
   const bool rel = pl.prec != SPH_PREC_FP32;
   std::vector<uint32_t> rank;
   rank_table(pl.dims, rank, S.morton_of_rank);
-  // staging: xa (x,y,z,0) | vr (vx,vy,vz,rho) | T | fid | x0 (x,y,z,0) | n0 | body | sid | rank
+  // staging: xa (x,y,z,0) | vr (vx,vy,vz,rho) | x0 (x,y,z,0) | n0 | T | fid | mat | body | sid | rank
   const size_t nm = pl.nmat > 1 ? nf : 0;
-  const size_t o_xa = 0, o_v = o_xa + 4 * nf * ps, o_T = o_v + 4 * nf * rs, o_fid = o_T + nf * ts,
-               o_mat = o_fid + nf * 4, o_x0 = o_mat + nm * 4, o_n0 = o_x0 + ns * 32, o_b = o_n0 + ns * 32,
+  const size_t o_xa = 0, o_v = o_xa + 4 * nf * ps, o_x0 = o_v + 4 * nf * rs, o_n0 = o_x0 + ns * 32,
+               o_T = o_n0 + ns * 32, o_fid = o_T + nf * ts, o_mat = o_fid + nf * 4, o_b = o_mat + nm * 4,
                o_sid = o_b + ns * 4, o_rank = o_sid + ns * 4, o_end = o_rank + rank.size() * 4;
-  S.staging.assign(o_end, 0);
-  std::vector<char>& B = S.staging;
-  auto put_real = [&](size_t off, size_t sz, size_t idx, double val) {
-    if (sz == 8) put<double>(B, off + idx * 8, val);
-    else put<float>(B, off + idx * 4, (float)val);
-  };
-  for (size_t i = 0; i < nf; ++i) {
-    for (size_t k = 0; k < 3; ++k) {
-      put_real(o_xa, ps, 4 * i + k, x[3 * i + k]);
-      put_real(o_v, rs, 4 * i + k, v ? v[3 * i + k] : 0.0);
+  S.staging.reset(new (std::nothrow) char[o_end]);
+  if (!S.staging) return fail(SPH_ERR_OOM, "host staging allocation failed");
+  char* B = S.staging.get();
+  auto fluid = [&](auto pos, auto real, auto temp) {
+    typedef decltype(pos) Pos;
+    typedef decltype(real) Real;
+    typedef decltype(temp) Temp;
+    Pos* px = (Pos*)(B + o_xa);
+    Real* pv = (Real*)(B + o_v);
+    Temp* pT = (Temp*)(B + o_T);
+    uint32_t *id = (uint32_t*)(B + o_fid), *pm = (uint32_t*)(B + o_mat);
+    for (size_t i = 0; i < nf; ++i) {
+      for (size_t k = 0; k < 3; ++k) {
+        px[4 * i + k] = (Pos)x[3 * i + k];
+        pv[4 * i + k] = v ? (Real)v[3 * i + k] : (Real)0;
+      }
+      px[4 * i + 3] = (Pos)0;
+      pv[4 * i + 3] = (Real)(rel ? rho[i] - rho0 : rho[i]);
+      pT[i] = (Temp)T[i];
+      id[i] = (uint32_t)i;
+      if (nm) pm[i] = material ? (uint32_t)material[i] : 0u;
     }
-    put_real(o_v, rs, 4 * i + 3, rel ? rho[i] - rho0 : rho[i]);
-    put_real(o_T, ts, i, T[i]);
-    put<uint32_t>(B, o_fid + i * 4, (uint32_t)i);
-    if (nm) put<uint32_t>(B, o_mat + i * 4, material ? (uint32_t)material[i] : 0u);
-  }
+  };
+  if (pl.prec == SPH_PREC_FP64) fluid(0.0, 0.0, 0.0);
+  else if (pl.prec == SPH_PREC_FP32) fluid(0.0f, 0.0f, 0.0f);
+  else fluid(0.0, 0.0f, 0.0);
+  double *px0 = (double*)(B + o_x0), *pn0 = (double*)(B + o_n0);
+  int32_t* pb = (int32_t*)(B + o_b);
+  uint32_t* ps_id = (uint32_t*)(B + o_sid);
   for (size_t w = 0; w < ns; ++w) {
     for (size_t k = 0; k < 3; ++k) {
-      put<double>(B, o_x0 + (4 * w + k) * 8, x0[3 * w + k]);
-      put<double>(B, o_n0 + (4 * w + k) * 8, n0[3 * w + k]);
+      px0[4 * w + k] = x0[3 * w + k];
+      pn0[4 * w + k] = n0[3 * w + k];
     }
-    put<int32_t>(B, o_b + w * 4, body[w]);
-    put<uint32_t>(B, o_sid + w * 4, (uint32_t)w);
+    px0[4 * w + 3] = pn0[4 * w + 3] = 0.0;
+    pb[w] = body[w];
+    ps_id[w] = (uint32_t)w;
   }
-  std::memcpy(B.data() + o_rank, rank.data(), rank.size() * 4);
+  std::memcpy(B + o_rank, rank.data(), rank.size() * 4);
   hipStream_t st = P->stream;
   const SlotDesc& D = S.d;
   HIPCHK(hipMemsetAsync(S.arena, 0, S.bytes, st));
-  HIPCHK(hipMemcpyAsync(D.xa, B.data() + o_xa, 4 * nf * ps, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(D.vr, B.data() + o_v, 4 * nf * rs, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(D.T, B.data() + o_T, nf * ts, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(D.fid, B.data() + o_fid, nf * 4, hipMemcpyHostToDevice, st));
-  if (nm) HIPCHK(hipMemcpyAsync(D.mat, B.data() + o_mat, nf * 4, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(D.xa, B + o_xa, 4 * nf * ps, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(D.vr, B + o_v, 4 * nf * rs, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(D.T, B + o_T, nf * ts, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(D.fid, B + o_fid, nf * 4, hipMemcpyHostToDevice, st));
+  if (nm) HIPCHK(hipMemcpyAsync(D.mat, B + o_mat, nf * 4, hipMemcpyHostToDevice, st));
   if (ns) {
-    HIPCHK(hipMemcpyAsync(D.x0, B.data() + o_x0, ns * 32, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(D.n0, B.data() + o_n0, ns * 32, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(D.body, B.data() + o_b, ns * 4, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(D.sid, B.data() + o_sid, ns * 4, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(D.x0, B + o_x0, ns * 32, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(D.n0, B + o_n0, ns * 32, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(D.body, B + o_b, ns * 4, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(D.sid, B + o_sid, ns * 4, hipMemcpyHostToDevice, st));
   }
-  HIPCHK(hipMemcpyAsync(D.rank, B.data() + o_rank, rank.size() * 4, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(D.rank, B + o_rank, rank.size() * 4, hipMemcpyHostToDevice, st));
   return SPH_OK;
 }
 
@@ -779,7 +788,7 @@ static int admit(sph_pool* P, const sph_params* p, int32_t nbody, const sph_body
   D.kW = 21.0 / (16.0 * M_PI * D.h * D.h * D.h);
   D.kF = -5.0 * D.kW / (D.h * D.h);
   double vtip = 0.0;
-  std::vector<double> rmax((size_t)nbody, 0.0);
+  std::vector<double> r2max((size_t)nbody, 0.0);
   for (int k = 0; k < nbody; ++k) {
     S.bodies[k] = b[k];
     const double an = std::sqrt(b[k].axis[0] * b[k].axis[0] + b[k].axis[1] * b[k].axis[1] + b[k].axis[2] * b[k].axis[2]);
@@ -804,10 +813,10 @@ static int admit(sph_pool* P, const sph_params* p, int32_t nbody, const sph_body
       const double d = u[a] - au * D.ba[k][a];
       d2 += d * d;
     }
-    rmax[(size_t)k] = std::max(rmax[(size_t)k], std::sqrt(d2));
+    r2max[(size_t)k] = std::max(r2max[(size_t)k], d2);
   }
   for (int k = 0; k < nbody; ++k) {
-    D.btip[k] = b[k].omega != 0.0 ? std::fabs(b[k].omega) * rmax[(size_t)k] : 0.0;
+    D.btip[k] = b[k].omega != 0.0 ? std::fabs(b[k].omega) * std::sqrt(r2max[(size_t)k]) : 0.0;
     vtip = std::max(vtip, D.btip[k]);
   }
   D.nac_bound = nac_bound(p, vtip);
@@ -1043,26 +1052,16 @@ static double get_as_double(const char* base, size_t idx, size_t sz) {
 }
 
 static int slot_get_fluid(sph_pool* P, SlotHost& S, double* x, double* v, double* rho, double* T) {
+  // put into the caller's order on the device, in the build's scratch rows
+  // (128 B per particle at least), which hold nothing between steps
+  const size_t nf = (size_t)S.plan.nf;
+  double *dx = (double*)S.d.rmaj, *dv = dx + 3 * nf, *dr = dv + 3 * nf, *dT = dr + nf;
+  HIPCHK(launch_export(P->prec, P->d_table, (int)(&S - P->slots), S.plan.nblk[DOM_FLUID], dx, dv, dr, dT, P->stream));
+  if (x) HIPCHK(hipMemcpyAsync(x, dx, 3 * nf * 8, hipMemcpyDeviceToHost, P->stream));
+  if (v) HIPCHK(hipMemcpyAsync(v, dv, 3 * nf * 8, hipMemcpyDeviceToHost, P->stream));
+  if (rho) HIPCHK(hipMemcpyAsync(rho, dr, nf * 8, hipMemcpyDeviceToHost, P->stream));
+  if (T) HIPCHK(hipMemcpyAsync(T, dT, nf * 8, hipMemcpyDeviceToHost, P->stream));
   HIPCHK(hipStreamSynchronize(P->stream));
-  const Plan& pl = S.plan;
-  const size_t nf = (size_t)pl.nf;
-  std::vector<uint32_t> fid(nf);
-  std::vector<char> xa(4 * nf * pl.pos_sz), dr(4 * nf * pl.real_sz), vv(4 * nf * pl.real_sz), tt(nf * pl.temp_sz);
-  LCHK(d2h(fid.data(), S.d.fid, nf * 4));
-  LCHK(d2h(xa.data(), S.d.xa, xa.size()));
-  LCHK(d2h(dr.data(), S.d.drift, dr.size()));
-  LCHK(d2h(vv.data(), S.d.vr, vv.size()));
-  LCHK(d2h(tt.data(), S.d.T, tt.size()));
-  const bool rel = pl.prec != SPH_PREC_FP32;
-  for (size_t k = 0; k < nf; ++k) {
-    const size_t o = fid[k];
-    for (size_t a = 0; a < 3; ++a) {
-      if (x) x[3 * o + a] = get_as_double(xa.data(), 4 * k + a, pl.pos_sz) + get_as_double(dr.data(), 4 * k + a, pl.real_sz);
-      if (v) v[3 * o + a] = get_as_double(vv.data(), 4 * k + a, pl.real_sz);
-    }
-    if (rho) rho[o] = get_as_double(vv.data(), 4 * k + 3, pl.real_sz) + (rel ? S.params.rho0 : 0.0);
-    if (T) T[o] = get_as_double(tt.data(), k, pl.temp_sz);
-  }
   return SPH_OK;
 }
 

@@ -171,4 +171,9 @@ int grid_domain(int kid, int which);
 hipError_t launch_contact(int prec, const SlotDesc* table, const LaunchTab& tab, double* zout, double* part,
                           double* mean, hipStream_t stream);
 
+// The fluid state of slot `slot` in the caller's order and FP64 (k_export):
+// positions and velocities (3 each), densities, temperatures.
+hipError_t launch_export(int prec, const SlotDesc* table, int slot, int nblk, double* x, double* v, double* rho,
+                         double* T, hipStream_t stream);
+
 }  // namespace sphk
