@@ -332,6 +332,7 @@ __global__ __launch_bounds__(BLOCK) void k_fold(const SlotDesc* table, LaunchTab
 // of the block sums, block-local scan plus offset).  Resets counts to serve as
 // scatter cursors.
 // ---------------------------------------------------------------------------
+template <int NW = BLOCK / WAVE>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds, uint32_t& total) {
   const int wv = threadIdx.x / WAVE, ln = threadIdx.x % WAVE;
   uint32_t x = v;
@@ -343,8 +344,12 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds, u
   if (ln == WAVE - 1) lds[wv] = x;
   __syncthreads();
   uint32_t off = 0;
-  for (int k = 0; k < wv; ++k) off += lds[k];
-  total = lds[0] + lds[1] + lds[2] + lds[3];
+  total = 0;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    off += k < wv ? lds[k] : 0u;
+    total += lds[k];
+  }
   __syncthreads();
   return off + x - v;
 }
@@ -641,23 +646,26 @@ __device__ __forceinline__ void run_candidates(const GLB Pos4* x, const uint32_t
 // run whose stencil holds its cell (a few tens of runs, 16 on the lattice).
 constexpr int MAXRUN = 64;
 constexpr uint16_t NO_ITEM = 0xffffu, ITEM_REF = 0x8000u;   // no particles; covered by entry (value & 0x7fff)
+constexpr unsigned CUS = 256;          // compute units of the card
+constexpr int WIDE = 4 * BLOCK;  // threads per block of the wide build
 struct StageTab {
   uint32_t home[MAXRUN];
   uint16_t id[2][27 * MAXRUN];       // the entry's item: fluid, solid
   BlkItem item[2][STAGE_ITEMS];
-  uint32_t scan[BLOCK / WAVE], last[BLOCK / WAVE];
+  uint32_t scan[WIDE / WAVE], last[BLOCK / WAVE], runs[BLOCK / WAVE];
   int cont1;                         // wavefront 1 starts within a run
 };
 
 // Fills the table for the runs [r0, r1) and writes the block's head, with the
 // given wavefronts staged, and list; returns whether the candidates fit.
+template <int NT>
 __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb, int lb, int r0, int r1, int waves) {
   const GLB uint32_t* rank = gpc<uint32_t>(S.rank);
   const GLB uint32_t* st[2] = {gpc<uint32_t>(S.start_f), gpc<uint32_t>(S.start_s)};
   const int n = 27 * r1;
   uint32_t done[2] = {0u, 0u};       // (cells << 21) | candidates numbered so far
   bool big = false;
-  for (int i0 = 27 * r0; i0 < n; i0 += BLOCK) {
+  for (int i0 = 27 * r0; i0 < n; i0 += NT) {
     const int it = i0 + (int)threadIdx.x;
     uint32_t f0[2] = {0u, 0u}, cnt[2] = {0u, 0u};
     int ref = -1;
@@ -693,7 +701,7 @@ __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
       uint32_t total;
-      const uint32_t at = done[a] + block_excl_scan((cnt[a] ? 1u << 21 : 0u) + cnt[a], tb.scan, total);
+      const uint32_t at = done[a] + block_excl_scan<NT / WAVE>((cnt[a] ? 1u << 21 : 0u) + cnt[a], tb.scan, total);
       done[a] += total;
       const uint32_t e = at >> 21;
       if (it < n) tb.id[a][it] = ref >= 0 ? (uint16_t)(ITEM_REF | ref) : cnt[a] ? (uint16_t)e : NO_ITEM;
@@ -711,7 +719,7 @@ __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
     if (a && (int)threadIdx.x < ni[1]) tb.item[1][threadIdx.x].base += (uint16_t)ns0;
-    for (int it = 27 * r0 + threadIdx.x; it < n; it += BLOCK) {
+    for (int it = 27 * r0 + threadIdx.x; it < n; it += NT) {
       const uint16_t v = tb.id[a][it];
       if (v != NO_ITEM && (v & ITEM_REF)) tb.id[a][it] = tb.id[a][v & 0x7fffu];
     }
@@ -720,99 +728,122 @@ __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb
   // the list, sixteen lanes per cell
 #pragma unroll
   for (int a = 0; a < 2; ++a)
-    for (int e = threadIdx.x >> 4; e < ni[a]; e += BLOCK / 16) {
+    for (int e = threadIdx.x >> 4; e < ni[a]; e += NT / 16) {
       const BlkItem x = tb.item[a][e];
       for (int k = threadIdx.x & 15; k < x.cnt; k += 16) list[x.base + k] = x.start + (uint32_t)k;
     }
   return true;
 }
 
-template <class P>
-__global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTab tab) {
+// NT threads build the rows of BLOCK particles: one thread per particle, each
+// wavefront with its own particles' runs, or (WIDE) four, so that four times as
+// many wavefronts share the block's runs.
+template <class P, int NT>
+__global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab tab) {
 #pragma clang fp contract(off)
   typedef typename P::Pos Pos;
   typedef typename P::Pos4 Pos4;
   typedef typename P::Real4 Real4;
   constexpr bool CANSTAGE = std::is_same<typename P::Real, float>::value;
-  __shared__ uint32_t lr_all[BLOCK / WAVE][6][32];
-  __shared__ StageTab tb;   // of the staged modes
+  __shared__ uint32_t lr_all[NT / WAVE][6][32];
+  __shared__ StageTab tb;
+  // the wavefronts' runs: first particle, cell, run of the block; per particle:
+  // row lengths, its own row entry
+  __shared__ uint16_t seg_first[BLOCK + 1], seg_run[BLOCK], len[2][BLOCK];
+  __shared__ uint32_t seg_cell[BLOCK], own_entry[BLOCK];
   SLOT_PROLOGUE(DOM_FLUID);
-  const int i = lb * BLOCK + threadIdx.x;
   const int nf = S.nf;
-  const bool act = i < nf;
-  const int ii = act ? i : nf - 1;
+  const int i = lb * BLOCK + threadIdx.x;
+  const bool act = threadIdx.x < BLOCK && i < nf;
   const int lane = threadIdx.x & (WAVE - 1);
   const int wv = threadIdx.x / WAVE;
   const GLB Pos4* xa = gpc<Pos4>(S.xa);
   const GLB Pos4* xw = gpc<Pos4>(S.xw);
-  const Pos4 xi4 = xa[ii];
-  const Pos xi = xi4.x, yi = xi4.y, zi = xi4.z;
-  int c[3];
-  cell_coords<Pos>(S, xi, yi, zi, c);
-  if (act) gp<Real4>(S.xo)[i] = cell_offset<P>(S, xi, yi, zi, c);
+  uint32_t pc = 0u;
+  if (threadIdx.x < BLOCK) {
+    const Pos4 x = xa[min(i, nf - 1)];
+    int c[3];
+    cell_coords<Pos>(S, x.x, x.y, x.z, c);
+    if (act) gp<Real4>(S.xo)[i] = cell_offset<P>(S, x.x, x.y, x.z, c);
+    pc = pack_cell(c);
+  }
   const double cut2 = S.cut2;
   const int kf = S.kf, ks = S.ks;
-  // runs of equal cells among the block's particles, then the wave's
-  const uint32_t pc = pack_cell(c);
+  // runs of equal cells among each wavefront's particles
   const uint32_t prevc = (uint32_t)__shfl_up((int)pc, 1, WAVE);
-  const int nact = __popcll(__ballot(act));
-  uint64_t runs = __ballot(act && (lane == 0 || prevc != pc));
-  bool staged = false;
-  int run = 0;
+  const uint64_t runs = __ballot(act && (lane == 0 || prevc != pc));
+  const uint64_t upto = lane == WAVE - 1 ? ~0ull : (2ull << lane) - 1;
+  if (wv < BLOCK / WAVE && lane == WAVE - 1) {
+    tb.runs[wv] = (uint32_t)__popcll(runs);
+    tb.last[wv] = pc;
+  }
+  __syncthreads();
+  int nseg = 0, seg = __popcll(runs & upto) - 1, seg0 = 0;   // seg0: the wavefront's own first run
+  for (int w = 0; w < BLOCK / WAVE; ++w) {
+    if (w < wv) seg0 += (int)tb.runs[w];
+    nseg += (int)tb.runs[w];
+  }
+  seg += seg0;
+  const bool head = (runs >> lane) & 1;
+  if (head) {
+    seg_first[seg] = (uint16_t)threadIdx.x;
+    seg_cell[seg] = pc;
+  }
+  if (threadIdx.x == 0) seg_first[nseg] = (uint16_t)min(BLOCK, nf - lb * BLOCK);
+  int waves = 0;   // the particles' wavefronts that are staged
   if constexpr (CANSTAGE) {
-    // the block's runs, numbered: a wave's first one may continue the last wave's
-    if (lane == WAVE - 1) tb.last[wv] = pc;
-    __syncthreads();
-    const bool cont = wv > 0 && tb.last[wv > 0 ? wv - 1 : 0] == (uint32_t)__builtin_amdgcn_readlane((int)pc, 0);
+    // the block's runs, numbered: a wavefront's first one may continue the last one's
+    const bool cont = wv > 0 && wv < BLOCK / WAVE && tb.last[max(wv - 1, 0)] == (uint32_t)__builtin_amdgcn_readlane((int)pc, 0);
     const uint64_t heads = cont ? runs & ~1ull : runs;
-    if (lane == 0) tb.scan[wv] = (uint32_t)__popcll(heads);
+    if (wv < BLOCK / WAVE && lane == 0) tb.scan[wv] = (uint32_t)__popcll(heads);
     if (threadIdx.x == WAVE) tb.cont1 = cont;
     __syncthreads();
-    int nruns = 0, cut1 = 0, cut3 = 0;   // runs that start in wavefront 0, in 0 to 2
+    int run = __popcll(heads & upto) - 1, nruns = 0, cut1 = 0, cut3 = 0;   // cut1, cut3: runs that start in wavefront 0, in 0 to 2
     for (int w = 0; w < BLOCK / WAVE; ++w) {
       if (w == 1) cut1 = nruns;
       if (w == 3) cut3 = nruns;
       if (w < wv) run += (int)tb.scan[w];
       nruns += (int)tb.scan[w];
     }
-    run += __popcll(heads & (lane == WAVE - 1 ? ~0ull : (2ull << lane) - 1)) - 1;
-    int waves = 0;
+    if (head) seg_run[seg] = (uint16_t)run;
     if (nruns <= MAXRUN) {
       if ((heads >> lane) & 1) tb.home[run] = pc;
       __syncthreads();
       // all four wavefronts, or the first or the last three
-      if (block_candidates(S, tb, lb, 0, nruns, 15)) waves = 15;
-      else if (block_candidates(S, tb, lb, 0, cut3, 7)) waves = 7;
-      else if (block_candidates(S, tb, lb, cut1 - tb.cont1, nruns, 14)) waves = 14;
+#pragma unroll 1
+      for (int a = 0; a < 3 && !waves; ++a) {
+        const int want = a == 0 ? 15 : a == 1 ? 7 : 14;
+        if (block_candidates<NT>(S, tb, lb, a == 2 ? cut1 - tb.cont1 : 0, a == 1 ? cut3 : nruns, want)) waves = want;
+      }
     }
     if (waves == 0 && threadIdx.x == 0) S.bhead[lb] = BlkHead{0, 0, 0, 0};
-    staged = (waves >> wv) & 1;
   }
+  __syncthreads();
   GLB uint32_t* rows = gp<uint32_t>(S.rmaj);
   const GLB uint32_t* rank = gpc<uint32_t>(S.rank);
   const GLB uint32_t* stf = gpc<uint32_t>(S.start_f);
   const GLB uint32_t* sts = gpc<uint32_t>(S.start_s);
   uint32_t (*lr)[32] = lr_all[wv];
   uint32_t *preF = lr[0], *preS = lr[1], *begF = lr[2], *begS = lr[3], *lclF = lr[4], *lclS = lr[5];
-  int cf = 0, cs = 0;
-  // this particle as a row entry
-  uint32_t own = (uint32_t)i;
-  if (staged && act) {
-    const BlkItem x = tb.item[0][tb.id[0][27 * run + 13]];
-    own = 16u * (x.base + (uint32_t)i - x.start) | 4u * 13u << 16;
-  }
   // this lane's offset in a 27-cell stencil
   const int ox = lane % 3 - 1, oy = (lane / 3) % 3 - 1, oz = lane / 9 - 1;
-  const int wbase = i - lane;
-  while (runs) {
-    const int L = __builtin_ctzll(runs);
-    runs &= runs - 1;
-    const int R = runs ? __builtin_ctzll(runs) : nact;
+  const int segs = (int)__popcll(runs);
+  for (int k = NT > BLOCK ? wv : seg0; k < (NT > BLOCK ? nseg : seg0 + segs); k += NT > BLOCK ? NT / WAVE : 1) {
+    const int first = __builtin_amdgcn_readfirstlane((int)seg_first[k]);
+    const int R = __builtin_amdgcn_readfirstlane((int)seg_first[k + 1]) - first;
+    const uint32_t cell = (uint32_t)__builtin_amdgcn_readfirstlane((int)seg_cell[k]);
+    const bool staged = CANSTAGE && ((waves >> (first / WAVE)) & 1);
+    const int wbase = lb * BLOCK + first;
+    const int q = wbase + min(lane, R - 1);
+    const Pos4 xq = xa[q];
+    uint32_t own = (uint32_t)q;
     uint32_t f0 = 0, f1 = 0, s0 = 0, s1 = 0, lf = 0, ls = 0;
     if (staged) {
-      const int e = 27 * __builtin_amdgcn_readlane(run, L) + lane;
+      const int e = 27 * __builtin_amdgcn_readfirstlane((int)seg_run[k]);
+      const BlkItem h = tb.item[0][tb.id[0][e + 13]];
+      own = 16u * (h.base + (uint32_t)q - h.start) | 4u * 13u << 16;
       if (lane < 27) {
-        const uint32_t a = tb.id[0][e], b = tb.id[1][e];
+        const uint32_t a = tb.id[0][e + lane], b = tb.id[1][e + lane];
         if (a != NO_ITEM) {
           const BlkItem x = tb.item[0][a];
           f0 = x.start;
@@ -827,8 +858,7 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
         }
       }
     } else {
-      const int nx = __builtin_amdgcn_readlane(c[0], L) + ox, ny = __builtin_amdgcn_readlane(c[1], L) + oy,
-                nz = __builtin_amdgcn_readlane(c[2], L) + oz;
+      const int nx = (int)(cell & 1023u) + ox, ny = (int)((cell >> 10) & 1023u) + oy, nz = (int)(cell >> 20) + oz;
       if (lane < 27 && nx >= 0 && ny >= 0 && nz >= 0 && nx < S.dims[0] && ny < S.dims[1] && nz < S.dims[2]) {
         const uint32_t r = rank[cell_linear(S, nx, ny, nz)];
         f0 = stf[r];
@@ -850,42 +880,58 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
     }
     wave_lds_sync();
     const uint32_t none = 0xfffffffeu;   // no solid candidate is the particle itself
+    int cf = 0, cs = 0;
     if (staged) {
-      run_candidates<true, Pos>(xa, preF, begF, lclF, Mf, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, 0, kf, cf, own);
+      run_candidates<true, Pos>(xa, preF, begF, lclF, Mf, 0, R, wbase, xq.x, xq.y, xq.z, cut2, rows, kf + ks, 0, kf, cf, own);
       if (Ms)
-        run_candidates<true, Pos>(xw, preS, begS, lclS, Ms, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, kf, ks, cs, none);
+        run_candidates<true, Pos>(xw, preS, begS, lclS, Ms, 0, R, wbase, xq.x, xq.y, xq.z, cut2, rows, kf + ks, kf, ks, cs, none);
     } else {
-      run_candidates<false, Pos>(xa, preF, begF, nullptr, Mf, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, 0, kf, cf, own);
+      run_candidates<false, Pos>(xa, preF, begF, nullptr, Mf, 0, R, wbase, xq.x, xq.y, xq.z, cut2, rows, kf + ks, 0, kf, cf, own);
       if (Ms)
-        run_candidates<false, Pos>(xw, preS, begS, nullptr, Ms, L, R, wbase, xi, yi, zi, cut2, rows, kf + ks, kf, ks, cs,
+        run_candidates<false, Pos>(xw, preS, begS, nullptr, Ms, 0, R, wbase, xq.x, xq.y, xq.z, cut2, rows, kf + ks, kf, ks, cs,
                                    none);
+    }
+    if (lane < R) {
+      own_entry[first + lane] = own;
+      len[0][first + lane] = (uint16_t)min(cf, 0xffff);
+      len[1][first + lane] = (uint16_t)min(cs, 0xffff);
     }
     wave_lds_sync();
   }
-  if (!act) return;
-  if (cf > kf || cs > ks) {
-    raise_flag(S, F_CAPACITY);
-    cf = min(cf, kf);
-    cs = min(cs, ks);
+  if (NT > BLOCK) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   }
-  S.nfc[i] = (uint32_t)cf;
-  S.nsc[i] = (uint32_t)cs;
-  // move this particle's row (written by the wave's lanes, still in cache)
-  // into the SELL layout: entry k of the wave's particles lands contiguous
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  const GLB uint32_t* RM = rows + (int64_t)i * (kf + ks);
+  // move the rows (written by the block's lanes, still in cache) into the SELL
+  // layout: entry k of a wavefront's particles lands contiguous
+  const int p = threadIdx.x % BLOCK, part = threadIdx.x / BLOCK;
+  const int ip = lb * BLOCK + p;
+  if (ip >= nf) return;
+  int cf = len[0][p], cs = len[1][p];
+  if (part == 0) {
+    if (cf > kf || cs > ks) raise_flag(S, F_CAPACITY);
+    S.nfc[ip] = (uint32_t)min(cf, kf);
+    S.nsc[ip] = (uint32_t)min(cs, ks);
+  }
+  cf = min(cf, kf);
+  cs = min(cs, ks);
+  const uint32_t own = own_entry[p];
+  const bool staged = CANSTAGE && ((waves >> (p / WAVE)) & 1);
+  constexpr int STEP = 4 * (NT / BLOCK);
+  const GLB uint32_t* RM = rows + (int64_t)ip * (kf + ks);
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
     const int cap = a ? ks : kf, n = a ? cs : cf;
-    GLB uint32_t* dst = gp<uint32_t>(a ? S.srec : S.nrec) + (int64_t)(i >> 6) * cap * WAVE;
+    GLB uint32_t* dst = gp<uint32_t>(a ? S.srec : S.nrec) + (int64_t)(ip >> 6) * cap * WAVE;
     if (a) RM += kf;
     if (staged) {
       // groups of four entries, filled up with the particle itself to a multiple
       // of eight, and to eight at least: the sweeps fetch a row's first eight
       // neighbours before they look at its length
       GLB u4* G = (GLB u4*)dst + lane;
-      for (int k = 0; k < max(8, (n + 7) & ~7); k += 4) {
+      for (int k = 4 * part; k < max(8, (n + 7) & ~7); k += STEP) {
         u4 e = *(const GLB u4*)(RM + k);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -894,7 +940,7 @@ __global__ __launch_bounds__(BLOCK) void k_build(const SlotDesc* table, LaunchTa
       }
     } else {
       GLB uint32_t* RS = dst + lane;
-      for (int k = 0; k < n; k += 4) {
+      for (int k = 4 * part; k < n; k += STEP) {
         const u4 e = *(const GLB u4*)(RM + k);
         const uint32_t ev[4] = {e.x, e.y, e.z, e.w};
 #pragma unroll
@@ -1084,16 +1130,20 @@ __global__ __launch_bounds__(BLOCK) void k_sumw(const SlotDesc* table, LaunchTab
 // candidate slots per lane of the dummy-velocity sweep: four (six waves per
 // SIMD) against eight (three waves) took it from 0.29 to 0.20 ms
 constexpr int CBW = 4;
-template <class P>
-__global__ __launch_bounds__(BLOCK) void k_wallvel(const SlotDesc* table, LaunchTab tab) {
+template <class P, int NT>
+__global__ __launch_bounds__(NT) void k_wallvel(const SlotDesc* table, LaunchTab tab) {
   typedef typename P::Real Real;
   typedef typename P::Real4 Real4;
-  __shared__ uint32_t lds_pre[BLOCK / WAVE][32];
-  __shared__ uint32_t lds_beg[BLOCK / WAVE][32];
+  __shared__ uint32_t lds_pre[NT / WAVE][32];
+  __shared__ uint32_t lds_beg[NT / WAVE][32];
+  // WIDE: the block's runs, shared by all wavefronts, and their sums
+  __shared__ uint32_t seg_runs[BLOCK / WAVE];
+  __shared__ uint16_t seg_first[NT > BLOCK ? BLOCK + 1 : 1];
+  __shared__ Real sums[NT > BLOCK ? 4 : 1][NT > BLOCK ? BLOCK : 1];
   SLOT_PROLOGUE(DOM_SOLID);
   const int w = lb * BLOCK + threadIdx.x;
   const int ns = S.ns;
-  const bool act = w < ns;
+  const bool act = threadIdx.x < BLOCK && w < ns;
   const int ww = act ? w : ns - 1;
   const int lane = threadIdx.x & (WAVE - 1);
   const int wv = threadIdx.x / WAVE;
@@ -1105,23 +1155,46 @@ __global__ __launch_bounds__(BLOCK) void k_wallvel(const SlotDesc* table, Launch
     const GLB Real4* vr = gpc<Real4>(S.vr);
     const GLB uint32_t* rank = gpc<uint32_t>(S.rank);
     const GLB uint32_t* stf = gpc<uint32_t>(S.start_f);
-    const Real4 ow = gpc<Real4>(S.so)[ww];
+    const GLB Real4* so = gpc<Real4>(S.so);
+    Real4 ow = so[ww];
     const uint32_t cw = unpack_index(ow.w);
-    const int c[3] = {(int)(cw & 1023u), (int)((cw >> 10) & 1023u), (int)(cw >> 20)};
     const Real cut2 = (Real)S.cut2, inv_h = (Real)(1.0 / S.h), kW = (Real)S.kW, csr = (Real)S.cs_r;
     uint32_t* pre = lds_pre[wv];
     uint32_t* beg = lds_beg[wv];
-    const uint32_t myr = rank[cell_linear(S, c[0], c[1], c[2])];
-    const uint32_t prevr = (uint32_t)__shfl_up((int)myr, 1, WAVE);
+    const uint32_t prevc = (uint32_t)__shfl_up((int)cw, 1, WAVE);
     const int nact = __popcll(__ballot(act));
-    uint64_t runs = __ballot(act && (lane == 0 || prevr != myr));
+    uint64_t runs = __ballot(act && (lane == 0 || prevc != cw));
+    int nseg = 0;
+    if (NT > BLOCK) {
+      if (wv < BLOCK / WAVE && lane == 0) seg_runs[wv] = (uint32_t)__popcll(runs);
+      __syncthreads();
+      int seg = __popcll(runs & (lane == WAVE - 1 ? ~0ull : (2ull << lane) - 1)) - 1;
+      for (int k = 0; k < BLOCK / WAVE; ++k) {
+        if (k < wv) seg += (int)seg_runs[k];
+        nseg += (int)seg_runs[k];
+      }
+      if ((runs >> lane) & 1) seg_first[seg] = (uint16_t)threadIdx.x;
+      if (threadIdx.x == 0) seg_first[nseg] = (uint16_t)min(BLOCK, ns - lb * BLOCK);
+      __syncthreads();
+    }
     const int ox = lane % 3 - 1, oy = (lane / 3) % 3 - 1, oz = lane / 9 - 1;
-    while (runs) {
-      const int L = __builtin_ctzll(runs);
-      runs &= runs - 1;
-      const int R = runs ? __builtin_ctzll(runs) : nact;
-      const int nx = __builtin_amdgcn_readlane(c[0], L) + ox, ny = __builtin_amdgcn_readlane(c[1], L) + oy,
-                nz = __builtin_amdgcn_readlane(c[2], L) + oz;
+    for (int k = wv; NT > BLOCK ? k < nseg : runs != 0; k += NT / WAVE) {
+      // the run's particles: lanes [L, R)
+      int L, R, first = 0;
+      if (NT > BLOCK) {
+        first = __builtin_amdgcn_readfirstlane((int)seg_first[k]);
+        L = 0;
+        R = __builtin_amdgcn_readfirstlane((int)seg_first[k + 1]) - first;
+        ow = so[lb * BLOCK + first + min(lane, R - 1)];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) acc[a] = (Real)0;
+      } else {
+        L = __builtin_ctzll(runs);
+        runs &= runs - 1;
+        R = runs ? __builtin_ctzll(runs) : nact;
+      }
+      const uint32_t cl = (uint32_t)__builtin_amdgcn_readlane((int)unpack_index(ow.w), L);
+      const int nx = (int)(cl & 1023u) + ox, ny = (int)((cl >> 10) & 1023u) + oy, nz = (int)(cl >> 20) + oz;
       const bool valid = lane < 27 && nx >= 0 && ny >= 0 && nz >= 0 && nx < S.dims[0] && ny < S.dims[1] &&
                          nz < S.dims[2];
       uint32_t f0 = 0, f1 = 0;
@@ -1191,6 +1264,17 @@ __global__ __launch_bounds__(BLOCK) void k_wallvel(const SlotDesc* table, Launch
         }
       }
       wave_lds_sync();
+      if (NT > BLOCK && lane < R) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) sums[a][first + lane] = acc[a];
+      }
+    }
+    if (NT > BLOCK) {
+      __syncthreads();
+      if (threadIdx.x < BLOCK) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) acc[a] = sums[a][threadIdx.x];
+      }
     }
   }
   if (!act) return;
@@ -2410,10 +2494,17 @@ static hipError_t launch_p(int kid, int which, int sub, const SlotDesc* T, const
     case SPH_K_SCATTER: hipLaunchKernelGGL(k_scatter, g, b, 0, st, T, L, which); break;
     case SPH_K_CELLSORT: hipLaunchKernelGGL(k_cellsort, g, b, 0, st, T, L, which); break;
     case SPH_K_REORDER: hipLaunchKernelGGL(k_reorder<P>, g, b, 0, st, T, L, which); break;
-    case SPH_K_BUILD: hipLaunchKernelGGL(k_build<P>, g, b, 0, st, T, L); break;
+    case SPH_K_BUILD:
+      // a grid that leaves CUs idle takes four times the wavefronts per block
+      if (g.x <= CUS) hipLaunchKernelGGL((k_build<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
+      else hipLaunchKernelGGL((k_build<P, BLOCK>), g, b, 0, st, T, L);
+      break;
     case SPH_K_SUMW: hipLaunchKernelGGL(k_sumw<P>, g, b, 0, st, T, L); break;
     case SPH_K_CONTACT: hipLaunchKernelGGL(k_contact<P>, g, b, 0, st, T, L, nullptr, nullptr); break;
-    case SPH_K_WALLVEL: hipLaunchKernelGGL(k_wallvel<P>, g, b, 0, st, T, L); break;
+    case SPH_K_WALLVEL:
+      if (g.x <= CUS) hipLaunchKernelGGL((k_wallvel<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
+      else hipLaunchKernelGGL((k_wallvel<P, BLOCK>), g, b, 0, st, T, L);
+      break;
     case SPH_K_DT: hipLaunchKernelGGL(k_dt, g, b, 0, st, T, L); break;
     case SPH_K_VISC_HEAT:
       // which = 1: with the first acoustic sub-step's half update and momentum
