@@ -221,7 +221,7 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
   double sx = 0.0, sy = 0.0, sz = 0.0;
   double px = 0.0, py = 0.0, pz = 0.0, phx = 0.0;
   bool need = false;
-  if (live_i) {
+  if (live_i && mine) {
     const GLB Real4* xo = gpc<Real4>(S.xo);
     const Real4 oi = xo[i];
     const uint32_t ci = unpack_index(oi.w);
@@ -229,18 +229,33 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
     Real ax = 0, ay = 0, az = 0;
     const int n = (int)S.nfc[i];
     const GLB uint32_t* R = gpc<uint32_t>(S.nrec) + (int64_t)(i >> 6) * S.kf * WAVE + lane;
-    for (int k = 0; k < n; ++k) {
-      // a staged row's entry names the particle in the block's list
-      const uint32_t e = staged ? ((const GLB uint32_t*)(row_groups(S, i) + (int64_t)(k >> 2) * WAVE))[k & 3]
-                                : ldnt(R + (int64_t)k * WAVE);
-      const uint32_t j = staged ? list[(e & 0xffffu) >> 4] : e;
-      Real rx, ry, rz;
-      pair_vec(oi, ci, xo[j], csr, rx, ry, rz);
-      const Real r2 = rx * rx + ry * ry + rz * rz;
-      const Real Fk = kernel_F(r2, rsq0(r2), inv_h, kF);
-      ax += Fk * rx;
-      ay += Fk * ry;
-      az += Fk * rz;
+    // eight at a time, so that their loads overlap; past the row's end the
+    // particle itself, whose pair adds zero
+    for (int k = 0; k < n; k += 8) {
+      uint32_t j[8];
+      if (staged) {
+        // a staged row's entries name the particles in the block's list
+        uint32_t e[8];
+        row_entries(row_load(row_groups(S, i), k), e);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) j[u] = list[(e[u] & 0xffffu) >> 4];
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) j[u] = ldnt(R + (int64_t)(k + u) * WAVE);
+      }
+      Real4 o[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) o[u] = xo[k + u < n ? j[u] : (uint32_t)i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        Real rx, ry, rz;
+        pair_vec(oi, ci, o[u], csr, rx, ry, rz);
+        const Real r2 = rx * rx + ry * ry + rz * rz;
+        const Real Fk = kernel_F(r2, rsq0(r2), inv_h, kF);
+        ax += Fk * rx;
+        ay += Fk * ry;
+        az += Fk * rz;
+      }
     }
     sx = (double)ax * vol;
     sy = (double)ay * vol;
