@@ -191,6 +191,7 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
   __shared__ double red[BLOCK / WAVE];
   __shared__ d2v E[2 * MAX_TEETH];
   __shared__ uint32_t blk_all[BLOCK / WAVE][WAVE];   // active quadrature blocks of a wavefront
+  __shared__ double outside[3][QMAX];                // each quadrature block's integral where all of it is outside
   // RQ workgroups per block of BLOCK particles: workgroup `quarter` takes its
   // WAVE particles, every wavefront forms their neighbour sums and wavefront
   // w integrates the exterior of the particles with lane % RQ == w (so the
@@ -204,6 +205,29 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
   const SlotDesc& S = table[tab.slot[sk]];
   if (!live(S)) return;
   ls_flank_table(g, E);
+  {
+    // the cells' offsets from the particle are the same for every particle
+    const double del = 0.25 * S.h, dv = del * del * del, cut = 2.0 * S.h, inv_h = 1.0 / S.h;
+    for (int q = threadIdx.x; q < nq; q += BLOCK) {
+      const uint32_t ent = qcells[q];
+      double ax = 0.0, ay = 0.0, az = 0.0;
+      for (int k = 0; k < 8; ++k) {
+        const double ex = -del * (2.0 * ((int)((ent >> 8) & 15u) - QK / 2) + (k & 1) + 0.5);
+        const double ey = -del * (2.0 * ((int)((ent >> 4) & 15u) - QK / 2) + ((k >> 1) & 1) + 0.5);
+        const double ez = -del * (2.0 * ((int)(ent & 15u) - QK / 2) + ((k >> 2) & 1) + 0.5);
+        const double r2 = (ex * ex + ey * ey) + ez * ez;
+        if (!(r2 < cut * cut)) continue;
+        const double t = 1.0 - 0.5 * sqrt(r2) * inv_h;
+        const double w = S.kF * t * t * t * dv;
+        ax += w * ex;
+        ay += w * ey;
+        az += w * ez;
+      }
+      outside[0][q] = ax;
+      outside[1][q] = ay;
+      outside[2][q] = az;
+    }
+  }
   constexpr bool CANSTAGE = std::is_same<Real, float>::value;
   bool staged = false;
   const GLB uint32_t* list = nullptr;
@@ -298,7 +322,7 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
       // one block per lane: its centre's phi bounds all its cells, so a block
       // with phi(centre) + half-diagonal <= -edge/2 has no cell outside, and
       // one with phi(centre) - half-diagonal >= edge/2 has every cell wholly
-      // outside (fraction 1, no evaluation of its cells)
+      // outside (fraction 1: its share is the table's)
       const int q = s + lane;
       uint32_t ent = 0;
       bool act = false, full = false;
@@ -316,16 +340,19 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
           act = !full && pc + QHALFDIAG * del > -0.5 * del;
         }
       }
-      const uint64_t mm = __ballot(act), mf = __ballot(full);
-      if (!(mm | mf)) continue;
-      // the blocks' codes compacted in lane order, those that need their
-      // cells' level set first, then their cells spread over the lanes
+      if (full) {
+        ax += outside[0][q];
+        ay += outside[1][q];
+        az += outside[2][q];
+      }
+      const uint64_t mm = __ballot(act);
+      if (!mm) continue;
+      // the other blocks' codes compacted in lane order, then their cells
+      // spread over the lanes
       const int nm = __popcll(mm);
       if (act) blk[__builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u))] = ent;
-      if (full) blk[nm + __builtin_amdgcn_mbcnt_hi((uint32_t)(mf >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mf, 0u))] = ent;
       relax_lds_sync();
-      const int ncm = 8 * nm, ncell = 8 * (nm + __popcll(mf));
-      for (int k = lane; k < ncell; k += WAVE) {
+      for (int k = lane; k < 8 * nm; k += WAVE) {
         const uint32_t eb = blk[k >> 3];
         const int a = 2 * ((int)((eb >> 8) & 15u) - QK / 2) + (k & 1);
         const int b = 2 * ((int)((eb >> 4) & 15u) - QK / 2) + ((k >> 1) & 1);
@@ -337,11 +364,8 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
         if (!(r2 < cut * cut)) continue;
         const double rr = sqrt(r2);
         if (qphi + rr <= -0.5 * del) continue;
-        double f = 1.0;
-        if (k < ncm) {
-          f = fmin(0.5 + ls_phi(g, E, yx, yy, yz) * inv_del, 1.0);
-          if (!(f > 0.0)) continue;
-        }
+        const double f = fmin(0.5 + ls_phi(g, E, yx, yy, yz) * inv_del, 1.0);
+        if (!(f > 0.0)) continue;
         const double t = 1.0 - 0.5 * rr * inv_h;
         const double F = S.kF * t * t * t;
         const double w = F * (f * dv);
