@@ -1,0 +1,158 @@
+"""Blocks of the neighbour build and the sweeps: every way in which a block of
+256 particles takes its neighbours, small and large grids, and the read-out.
+
+A block stages the records of all particles its rows can name (at most 2432,
+of at most 64 runs of equal cells), or of three of its four wavefronts, or it
+gathers.  Bars: neighbour sets bit for bit; one step against the FP64 oracle to
+the bars of one step from identical state (1e-5 mixed, 1e-10 FP64, normalised
+as in test_gpu_parity); results that must not depend on the grid, and copies,
+exactly.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2512_09904_amd import cases
+
+pytestmark = pytest.mark.gpu
+
+BLOCK, WAVE, CAP, RUNS = 256, 64, 2432, 64
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module")
+def sph():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_09904_amd import sph as S
+    S.lib()
+    return S
+
+
+def _tank(keep):
+    """The 2 mm tank with the fluid particles of which keep(index) holds."""
+    c = cases.tank_c1(seed=7)
+    k = keep(np.arange(c.nf))
+    c.xf, c.vf, c.rhof, c.Tf = c.xf[k], c.vf[k], c.rhof[k], c.Tf[k]
+    return c
+
+
+def _kinds(ora, c):
+    """How each block of the sorted fluid takes its neighbours: 'whole',
+    'three' (the first or the last three wavefronts staged), 'gather'."""
+    rc, order = ora.sort_order(c.params, c.xf, np.arange(c.nf, dtype=np.uint32))
+    _, cf = ora.cells(c.params, c.xf[order])
+    xs, _, _ = ora.body_pose(c.bodies, c.xs0, c.ns0, c.body, 0.0)
+    _, cs = ora.cells(c.params, xs)
+    count = lambda cells: {tuple(k): int(n) for k, n in zip(*np.unique(cells, axis=0, return_counts=True))}
+    nf, ns = count(cf), count(cs)
+    off = np.array([(x, y, z) for z in (-1, 0, 1) for y in (-1, 0, 1) for x in (-1, 0, 1)])
+
+    def candidates(cells):
+        q = {tuple(k) for k in (np.unique(cells, axis=0)[:, None, :] + off[None]).reshape(-1, 3)}
+        return -(-sum(nf.get(k, 0) for k in q) // WAVE) * WAVE + sum(ns.get(k, 0) for k in q)
+
+    out = []
+    for b in range(0, c.nf, BLOCK):
+        cells = np.asarray(cf[b:b + BLOCK])
+        runs = 1 + int(np.sum(np.any(np.diff(cells, axis=0), axis=1)))
+        if runs > RUNS:
+            out.append("gather")
+        elif candidates(cells) <= CAP:
+            out.append("whole")
+        elif candidates(cells[:3 * WAVE]) <= CAP or (len(cells) > WAVE and candidates(cells[WAVE:]) <= CAP):
+            out.append("three")
+        else:
+            out.append("gather")
+    return out
+
+
+@pytest.mark.parametrize("precision,bar", [("mixed", 1e-5), ("fp64", 1e-10)])
+@pytest.mark.parametrize("name,keep,want", [
+    ("tank", lambda k: k >= 0, {"whole", "three"}),
+    ("ragged", lambda k: (k < BLOCK + 65) & (k % 41 != 0), {"whole"}),
+    ("thinned", lambda k: k % 13 == 0, {"gather"}),
+    ("isolated", lambda k: k % 997 == 5, {"whole"}),
+    ("one", lambda k: k == 4000, {"whole"}),
+])
+def test_rows_of_every_kind_of_block(sph, ora, precision, bar, name, keep, want):
+    """Neighbour sets and one step where blocks are staged whole, in part or not
+    at all: whole tanks, a ragged end, more runs than are numbered, particles
+    without fluid neighbours."""
+    c = _tank(keep)
+    kinds = _kinds(ora, c)
+    say("blocks", name, precision, c.nf, {k: kinds.count(k) for k in set(kinds)})
+    assert want <= set(kinds)
+    xs, _, _ = ora.body_pose(c.bodies, c.xs0, c.ns0, c.body, 0.0)
+    nb = ora.Nbr(c.params, c.xf, xs)
+    d = ora.timestep(c.params, c.bodies, c.xs0, c.body, c.vf)
+    dt, nac = d["dt_ad"], d["n_ac"]
+    o = ora.State(c, fixed_dt_ad=dt, fixed_nac=nac)
+    ro = o.step()
+    s = sph.Solver(c, precision=precision, fixed_dt_ad=dt, fixed_nac=nac)
+    fl, so = s.neighbour_sets()
+    assert fl == nb.sets(0)
+    assert so == nb.sets(1)
+    s.step(1)
+    rg = s.reduce()
+    g = s.get_fluid()
+    s.close()
+    p, umax = c.params, c.meta["umax"]
+    scale = dict(x=p["dp"], v=umax, rho=p["rho0"] * (umax / p["c0"]) ** 2, T=abs(c.bodies[0].T - c.Tf.mean()))
+    e = {k: np.max(np.abs(g[k] - getattr(o, k))) / q for k, q in scale.items()}
+    say("normalised errors", e)
+    assert max(e.values()) <= bar, e
+    assert rg["n_ac"] == ro["n_ac"]
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp32", "fp64"])
+def test_small_and_large_grids_agree(sph, precision):
+    """A grid of up to 256 blocks builds its rows and dummy velocities with four
+    times the wavefronts per block.  A small tank gives the same bits alone
+    (small grids) and beside one that makes both grids larger."""
+    a, b = cases.tank_c1(seed=8), cases.tank_c1(seed=9, dp=1.15e-3)
+    blocks = lambda n: -(-n // BLOCK)
+    say("grids", precision, blocks(a.nf), blocks(a.ns), blocks(a.nf) + blocks(b.nf), blocks(a.ns) + blocks(b.ns))
+    assert max(blocks(a.nf), blocks(a.ns)) <= 256
+    assert min(blocks(a.nf) + blocks(b.nf), blocks(a.ns) + blocks(b.ns)) > 256
+    res = []
+    for reqs in ([a], [b, a]):
+        pool = sph.Pool(1 << 40, max_slots=2, precision=precision)
+        slots = [pool.admit(c, 3) for c in reqs]
+        pool.step(3)
+        done = False
+        while not done:
+            done, rep = pool.poll(slots[-1])
+        res.append((pool.get_fluid(slots[-1]), rep))
+        pool.close()
+    (f0, r0), (f1, r1) = res
+    for k in ("x", "v", "rho", "T"):
+        assert np.array_equal(f0[k], f1[k]), k
+    assert r0["t"] == r1["t"] and r0["kinetic"] == r1["kinetic"]
+    for x, y in zip(r0["bodies"], r1["bodies"]):
+        assert np.array_equal(x["force"], y["force"]) and np.array_equal(x["torque"], y["torque"])
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp32", "fp64"])
+@pytest.mark.parametrize("nf", [1, 255, 257])
+def test_fields_read_back_in_the_callers_order(sph, precision, nf):
+    """The fields read back are the stored state (anchor plus drift, velocity,
+    density, temperature), particle by particle, at the edges of a block."""
+    c = _tank(lambda k: (k >= 3000) & (k < 3000 + nf))
+    s = sph.Solver(c, precision=precision)
+    s.step(2)
+    s.reduce()
+    g = s.get_fluid()
+    fid = s.dump("fluid_ids").astype(np.int64)
+    st = s.dump("fluid_state").reshape(nf, 16)
+    s.close()
+    assert np.array_equal(np.sort(fid), np.arange(nf))
+    assert np.array_equal(g["x"][fid], st[:, 0:3] + st[:, 3:6])
+    assert np.array_equal(g["v"][fid], st[:, 6:9])
+    assert np.array_equal(g["rho"][fid], st[:, 9])
+    assert np.array_equal(g["T"][fid], st[:, 11])
