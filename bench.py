@@ -56,10 +56,11 @@ def sweep_bytes(kernel, nf, nsr, pf, ps, prec="mixed"):
     """Algorithmic HBM bytes of one launch: each array touched once, rows streamed.
 
     `nsr` is the number of distinct solid particles that appear in some
-    fluid particle's row (the wall arrays read).  A row entry is the
-    neighbour's 4-byte index; the pair vector comes from the cell-relative
-    positions (one 4-wide record per particle).  The neighbour-state gathers
-    re-read arrays already counted once.
+    fluid particle's row (the wall arrays read).  A row entry is
+    4 bytes (the neighbour's number in the block and its stencil cell, or its
+    index); the pair vector comes from the cell-relative positions (one 4-wide
+    record per particle).  The neighbour records, loaded once per block or
+    gathered, re-read arrays already counted once.
     """
     rb = 8 if prec == "fp64" else 4          # Real
     pb = 4 if prec == "fp32" else 8          # Pos, Temp
@@ -70,8 +71,9 @@ def sweep_bytes(kernel, nf, nsr, pf, ps, prec="mixed"):
         # vr, offsets, ah, counts read; vrn written; drift read and written; wall offsets, lever arms
         return nf * (v4 + v4 + v4 + cnt + v4 + 2 * v4) + rows + nsr * 2 * v4
     if kernel == "continuity":
-        # vrn, offsets, counts read; drho and vr written; wall offsets, normals, velocities
-        return nf * (v4 + v4 + cnt + rb + v4) + rows + nsr * 3 * v4
+        # vrn, offsets, counts read; drho and vr written; wall offsets, and normals
+        # with the wall's normal velocity
+        return nf * (v4 + v4 + cnt + rb + v4) + rows + nsr * 2 * v4
     if kernel == "visc_heat":
         # with the first sub-step's momentum: vr, offsets, T, Drho, the 16-byte (T, Drho) records
         # of the neighbour gathers, counts read; ah and vrn written; drift read and written; wall
@@ -614,9 +616,9 @@ def main():
                           for k in sph.KERNELS if len(kt[k])}
     log("per-step kernel ms:", json.dumps({k: round(v, 4) for k, v in per_step_kernel_ms.items()}))
     nsr = distinct_wall_particles(s, case.nf)
-    # lane gathers of neighbour records per launch (16-B records in mixed precision; the viscous/heat
-    # sweep's fluid pairs: offsets, velocity state, the (T, Drho) record, and the material index with
-    # two materials)
+    # neighbour records read per launch, a lane each (16 B in mixed precision; from LDS where a block's
+    # records are staged, but for the viscous/heat sweep's (T, Drho) records and material indices):
+    # offsets, velocity state, and in that sweep's fluid pairs the other two
     gathers = {"momentum": 2 * (pf2 + ps2), "continuity": 2 * pf2 + 3 * ps2,
                "visc_heat": (4 if args.materials else 3) * pf2 + 3 * ps2, "sumw": 2 * (pf2 + ps2)}
     kern = {}

@@ -110,8 +110,8 @@ static int make_plan(const sph_params* p, int prec, int64_t nf, int64_t ns, Plan
   P->nf = nf;
   P->ns = ns;
   P->ncells = (int32_t)ncell;
-  // capacities are rounded up to multiples of 4 (rows are walked 4 at a time)
-  // multiples of sixteen: the sweeps read whole row groups of up to 16 entries
+  // capacities are rounded up to multiples of sixteen: the sweeps read whole
+  // groups of up to 16 row entries
   P->kf = ((p->max_fluid_nbrs > 0 ? p->max_fluid_nbrs : 128) + 15) & ~15;
   P->ks = ((p->max_solid_nbrs > 0 ? p->max_solid_nbrs : 96) + 15) & ~15;
   if (P->kf > 1024 || P->ks > 1024) return fail(SPH_ERR_ARG, "neighbour capacity above 1024");

@@ -7,10 +7,26 @@
 // steps many independent solves (continuous batching) and a solve's result
 // does not depend on which other slots share the launch.
 //
-// No MFMA: the sweeps are gathers over neighbour rows, bound by HBM and
-// cache bandwidth.  Reductions are deterministic (fixed-order wave
-// butterflies and block trees, Neumaier-compensated FP64 for the reports);
-// the only atomics are integer counters of the cell sort and fault flags.
+// No MFMA: the sweeps are sums over neighbour rows, bound by the rows' bytes and
+// by vector issue; the build's cutoff test as a matrix product (FP32, exact
+// retest near the cutoff) was 5 % faster at 1.9 M particles in one form and 39 %
+// slower in another, because placing the hits in order costs as much as the
+// test.  Reductions are deterministic (fixed-order wave butterflies and block
+// trees, Neumaier-compensated FP64 for the reports); the only atomics are
+// integer counters of the cell sort and fault flags.
+//
+// In FP32 and mixed arithmetic the sweeps take their neighbours from LDS.  A
+// block of 256 particles reaches about 2080 others (its cells' stencils), each
+// of them about ten times; their records are loaded once per block and the rows
+// name them by their number in the block.  Gathered from memory, the same
+// records are bound by the rate of scattered lanes.  Kernel times at 1.9 M
+// particles, gathered and staged: continuity 431 and 281 us, momentum 484 and
+// 343, viscous/heat 781 and 564, kernel sum 450 and 378; at 0.9 M 103 and 69,
+// 87 and 64, 406 and 282, 243 and 214.  What is left at 1.9 M (continuity): 0.89
+// GB fetched, 0.19 ms at the rate of a large copy, beside 0.2 ms of vector
+// instructions; two blocks fit a CU, and they overlap the two in part.
+// A block in ten has too many candidates for half a CU's LDS; three of its
+// wavefronts are staged then and the fourth gathers.
 #include <math.h>
 
 #include <type_traits>
@@ -19,10 +35,12 @@
 
 namespace sphk {
 
-// Rows are walked ROW_UNROLL entries at a time (SOLID_UNROLL for the wall
-// rows, VISC_SOLID_UNROLL for the viscous/heat sweep's wall rows, CONT_UNROLL
-// in the continuity sweep, which runs fastest with twelve gathers in flight
-// at three waves per SIMD: group sizes measured per sweep), and the next
+// Gathered rows (FP64 mode, and the wavefronts whose candidates do not fit) are
+// walked ROW_UNROLL entries at a time (SOLID_UNROLL for the wall rows,
+// VISC_SOLID_UNROLL for the viscous/heat sweep's wall rows, CONT_UNROLL in the
+// continuity sweep of the staged modes, where a block waits for its gathering
+// wavefront: with eight it took 287 us at 1.9 M particles, with twelve 281; in
+// FP64 twelve spilled, 287 us at 196,000 particles against 116), and the next
 // group's indices are loaded before the current group's gathers are
 // consumed, so a wavefront keeps two dependent loads in flight.  Entries past
 // a row's count are loaded from within the row's capacity (capacities are
@@ -39,12 +57,11 @@ namespace sphk {
 // block's own BLOCK (clamped to the array), staged in LDS with coalesced
 // loads.  In the Morton order most neighbours of the block's particles fall
 // inside it, so their 32-byte gathers become LDS reads; the rest are gathered
-// from global memory.  Used by the FP64 kernel-sum sweep, whose anchor
-// gathers (two 16-byte requests per pair) otherwise bound it by the vector
-// memory unit's rate of one scattered lane per clock.  512 particles (16 KB
-// of LDS per block) rather than 1024: fewer neighbours fall inside, but twice
-// as many blocks fit on a CU, which the sweep gains more from beside the
-// dummy-velocity sweep on the other stream.
+// from global memory.  Used by the kernel sums of blocks that are not staged,
+// whose anchor gathers (two 16-byte requests per pair) otherwise bound them by
+// the vector memory unit's rate of one scattered lane per clock.  512 particles
+// (16 KB of LDS per block) rather than 1024: fewer neighbours fall inside, but
+// twice as many blocks fit on a CU.
 constexpr int WIN = 512;
 struct Window {
   uint32_t w0, wn;
@@ -138,9 +155,8 @@ struct BodyAcc {
 // Deterministic block reduction of per-thread body accumulators: for each
 // body and component, the wavefront by DPP lane moves in a fixed order, then
 // the four waves in order.  A wavefront skips the bodies none of its lanes
-// touches (by LDS permutes over all bodies and components the reduction took
-// about a quarter of the momentum sweep on a tank: 0.41 against 0.30 ms at
-// 1.9 M particles).
+// touches (by LDS permutes over all bodies and components the momentum sweep
+// took 411 instead of 396 us at 1.9 M particles).
 template <int W>
 // out is quantity-major: out[(b * W + k) * nblk + lb]
 __device__ __forceinline__ void block_body_reduce(const BodyAcc<W> acc, int nbody, double* out, size_t nblk,
@@ -524,6 +540,10 @@ __global__ __launch_bounds__(BLOCK) void k_reorder(const SlotDesc* table, Launch
 // refreshed once per advection step).  The cutoff test d^2 < (2h)^2 is FP64
 // with d^2 = (dx dx + dy dy) + dz dz and no contraction.  Every particle also
 // stores its cell-relative position, from which the sweeps form r_ij.
+//
+// Bound by the candidate loop's instructions: 1.9 M particles take 1014 us with
+// the vector units 72 % busy at five waves per SIMD; numbering the candidates is
+// 70 us of it (939 without).
 //
 // A wavefront holds 64 consecutive particles of the Morton order, i.e. runs
 // of particles sharing a cell.  For each run the candidates of its 27-cell
@@ -2495,13 +2515,17 @@ static hipError_t launch_p(int kid, int which, int sub, const SlotDesc* T, const
     case SPH_K_CELLSORT: hipLaunchKernelGGL(k_cellsort, g, b, 0, st, T, L, which); break;
     case SPH_K_REORDER: hipLaunchKernelGGL(k_reorder<P>, g, b, 0, st, T, L, which); break;
     case SPH_K_BUILD:
-      // a grid that leaves CUs idle takes four times the wavefronts per block
+      // A grid of one block per CU at most lasts as long as one wavefront's runs:
+      // sixteen wavefronts per block share them (48 blocks: 117 -> 61 us, 196
+      // blocks: 120 -> 69).  Larger grids fill the CUs by themselves, and there
+      // the sharing costs a barrier (7437 blocks: 1047 us against 1014).
       if (g.x <= CUS) hipLaunchKernelGGL((k_build<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
       else hipLaunchKernelGGL((k_build<P, BLOCK>), g, b, 0, st, T, L);
       break;
     case SPH_K_SUMW: hipLaunchKernelGGL(k_sumw<P>, g, b, 0, st, T, L); break;
     case SPH_K_CONTACT: hipLaunchKernelGGL(k_contact<P>, g, b, 0, st, T, L, nullptr, nullptr); break;
     case SPH_K_WALLVEL:
+      // as the build (92 blocks: 68 -> 28 us)
       if (g.x <= CUS) hipLaunchKernelGGL((k_wallvel<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
       else hipLaunchKernelGGL((k_wallvel<P, BLOCK>), g, b, 0, st, T, L);
       break;
@@ -2535,8 +2559,9 @@ static hipError_t launch_p(int kid, int which, int sub, const SlotDesc* T, const
 }
 
 // K: the fluid state in the caller's order, FP64.  Bound by the scattered
-// stores (64 B per particle); 0.9 M particles take 60 us, against 14 ms for the
-// same reordering on the host.
+// stores (64 B per particle); a thread per sorted particle, so that the loads
+// are contiguous.  Reading back 0.9 M particles took 26 ms with the reordering
+// on the host and takes 6.4, nearly all of it the copy to the host.
 template <class P>
 __global__ __launch_bounds__(BLOCK) void k_export(const SlotDesc* table, int slot, double* x, double* v, double* rho,
                                                   double* T) {
