@@ -667,7 +667,7 @@ __device__ __forceinline__ void run_candidates(const GLB Pos4* x, const uint32_t
 constexpr int MAXRUN = 64;
 constexpr uint16_t NO_ITEM = 0xffffu, ITEM_REF = 0x8000u;   // no particles; covered by entry (value & 0x7fff)
 constexpr unsigned CUS = 256;          // compute units of the card
-constexpr int WIDE = 4 * BLOCK;  // threads per block of the wide build
+constexpr int WIDE = 4 * BLOCK;  // threads per block of the widest build
 struct StageTab {
   uint32_t home[MAXRUN];
   uint16_t id[2][27 * MAXRUN];       // the entry's item: fluid, solid
@@ -756,8 +756,8 @@ __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb
 }
 
 // NT threads build the rows of BLOCK particles: one thread per particle, each
-// wavefront with its own particles' runs, or (WIDE) four, so that four times as
-// many wavefronts share the block's runs.
+// wavefront with its own particles' runs, or (WIDE, WIDE / 2) four or two, so
+// that as many times the wavefronts share the block's runs.
 template <class P, int NT>
 __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab tab) {
 #pragma clang fp contract(off)
@@ -2515,18 +2515,27 @@ static hipError_t launch_p(int kid, int which, int sub, const SlotDesc* T, const
     case SPH_K_CELLSORT: hipLaunchKernelGGL(k_cellsort, g, b, 0, st, T, L, which); break;
     case SPH_K_REORDER: hipLaunchKernelGGL(k_reorder<P>, g, b, 0, st, T, L, which); break;
     case SPH_K_BUILD:
-      // A grid of one block per CU at most lasts as long as one wavefront's runs:
-      // sixteen wavefronts per block share them (48 blocks: 117 -> 61 us, 196
-      // blocks: 120 -> 69).  Larger grids fill the CUs by themselves, and there
-      // the sharing costs a barrier (7437 blocks: 1047 us against 1014).
+      // A grid that is resident at once lasts as long as one wavefront's runs, so
+      // more wavefronts per block share them: sixteen where every block has a CU
+      // of its own (48 blocks: 117 -> 61 us, 196 blocks: 120 -> 69), eight while
+      // the blocks of 512 threads still fit together, two per CU in mixed
+      // arithmetic, three in FP32 and FP64 (mixed: 313 blocks 133 -> 95 us, 469
+      // 147 -> 105, but 664 148 -> 153; FP32, 766 blocks: 152 -> 118, FP64 139 ->
+      // 123).  Larger grids fill the CUs by themselves, and there the sharing
+      // costs a barrier (7437 blocks: 1047 us against 1014).
       if (g.x <= CUS) hipLaunchKernelGGL((k_build<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
+      else if (g.x <= (sizeof(typename P::Pos) != sizeof(typename P::Real) ? 2 : 3) * CUS)
+        hipLaunchKernelGGL((k_build<P, WIDE / 2>), g, dim3(WIDE / 2), 0, st, T, L);
       else hipLaunchKernelGGL((k_build<P, BLOCK>), g, b, 0, st, T, L);
       break;
     case SPH_K_SUMW: hipLaunchKernelGGL(k_sumw<P>, g, b, 0, st, T, L); break;
     case SPH_K_CONTACT: hipLaunchKernelGGL(k_contact<P>, g, b, 0, st, T, L, nullptr, nullptr); break;
     case SPH_K_WALLVEL:
-      // as the build (92 blocks: 68 -> 28 us)
+      // as the build (92 blocks: 68 -> 28 us, 350: 110 -> 76, 540 in FP32: 89 -> 59); three blocks of 512 threads fit
+      // a CU in FP32 and mixed arithmetic, one in FP64
       if (g.x <= CUS) hipLaunchKernelGGL((k_wallvel<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
+      else if (sizeof(typename P::Real) == 4 && g.x <= 3 * CUS)
+        hipLaunchKernelGGL((k_wallvel<P, WIDE / 2>), g, dim3(WIDE / 2), 0, st, T, L);
       else hipLaunchKernelGGL((k_wallvel<P, BLOCK>), g, b, 0, st, T, L);
       break;
     case SPH_K_DT: hipLaunchKernelGGL(k_dt, g, b, 0, st, T, L); break;

@@ -112,17 +112,19 @@ def test_rows_of_every_kind_of_block(sph, ora, precision, bar, name, keep, want)
 
 @pytest.mark.parametrize("precision", ["mixed", "fp32", "fp64"])
 def test_small_and_large_grids_agree(sph, precision):
-    """A grid of up to 256 blocks builds its rows and dummy velocities with four
-    times the wavefronts per block.  A small tank gives the same bits alone
-    (small grids) and beside one that makes both grids larger."""
+    """Grids of up to 256 and 768 blocks build their rows and dummy velocities
+    with four times and twice the wavefronts per block.  A small tank gives the
+    same bits alone and beside others that take both grids past these lines."""
     a, b = cases.tank_c1(seed=8), cases.tank_c1(seed=9, dp=1.15e-3)
     blocks = lambda n: -(-n // BLOCK)
     say("grids", precision, blocks(a.nf), blocks(a.ns), blocks(a.nf) + blocks(b.nf), blocks(a.ns) + blocks(b.ns))
     assert max(blocks(a.nf), blocks(a.ns)) <= 256
-    assert min(blocks(a.nf) + blocks(b.nf), blocks(a.ns) + blocks(b.ns)) > 256
+    assert 256 < min(blocks(a.nf) + blocks(b.nf), blocks(a.ns) + blocks(b.ns))
+    assert max(blocks(a.nf) + blocks(b.nf), blocks(a.ns) + blocks(b.ns)) <= 512
+    assert min(blocks(a.nf) + 4 * blocks(b.nf), blocks(a.ns) + 4 * blocks(b.ns)) > 768
     res = []
-    for reqs in ([a], [b, a]):
-        pool = sph.Pool(1 << 40, max_slots=2, precision=precision)
+    for reqs in ([a], [b, a], 4 * [b] + [a]):
+        pool = sph.Pool(1 << 40, max_slots=len(reqs), precision=precision)
         slots = [pool.admit(c, 3) for c in reqs]
         pool.step(3)
         done = False
@@ -130,12 +132,13 @@ def test_small_and_large_grids_agree(sph, precision):
             done, rep = pool.poll(slots[-1])
         res.append((pool.get_fluid(slots[-1]), rep))
         pool.close()
-    (f0, r0), (f1, r1) = res
-    for k in ("x", "v", "rho", "T"):
-        assert np.array_equal(f0[k], f1[k]), k
-    assert r0["t"] == r1["t"] and r0["kinetic"] == r1["kinetic"]
-    for x, y in zip(r0["bodies"], r1["bodies"]):
-        assert np.array_equal(x["force"], y["force"]) and np.array_equal(x["torque"], y["torque"])
+    f0, r0 = res[0]
+    for f1, r1 in res[1:]:
+        for k in ("x", "v", "rho", "T"):
+            assert np.array_equal(f0[k], f1[k]), k
+        assert r0["t"] == r1["t"] and r0["kinetic"] == r1["kinetic"]
+        for x, y in zip(r0["bodies"], r1["bodies"]):
+            assert np.array_equal(x["force"], y["force"]) and np.array_equal(x["torque"], y["torque"])
 
 
 @pytest.mark.parametrize("precision", ["mixed", "fp32", "fp64"])
