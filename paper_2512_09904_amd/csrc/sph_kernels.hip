@@ -771,7 +771,8 @@ __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab t
   // row lengths, its own row entry
   __shared__ uint16_t seg_first[BLOCK + 1], seg_run[BLOCK], len[2][BLOCK];
   __shared__ uint32_t seg_cell[BLOCK], own_entry[BLOCK];
-  SLOT_PROLOGUE(DOM_FLUID);
+  SLOT_FIND(DOM_FLUID);
+  if (!live_block(S)) return;
   const int nf = S.nf;
   const int i = lb * BLOCK + threadIdx.x;
   const bool act = threadIdx.x < BLOCK && i < nf;
@@ -1535,7 +1536,7 @@ __global__ __launch_bounds__(BLOCK)
   const Temp Ti = T[ii];
   const Real drhoi = gpc<Real>(S.drho)[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
-  if (!live(S)) return;
+  if (!live_block(S)) return;
   const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   const bool mats = MAT && S.mat != nullptr;
   if (mats) {
@@ -1947,7 +1948,7 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
   const Real4 vi = vr[ii];
   const Real4 oi = xo[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
-  if (!live_sub(S, sub)) return;
+  if (!live_block(S, sub)) return;
   const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
   if constexpr (CANSTAGE) {
