@@ -1056,12 +1056,19 @@ static int slot_get_fluid(sph_pool* P, SlotHost& S, double* x, double* v, double
   // (128 B per particle at least), which hold nothing between steps
   const size_t nf = (size_t)S.plan.nf;
   double *dx = (double*)S.d.rmaj, *dv = dx + 3 * nf, *dr = dv + 3 * nf, *dT = dr + nf;
-  HIPCHK(launch_export(P->prec, P->d_table, (int)(&S - P->slots), S.plan.nblk[DOM_FLUID], dx, dv, dr, dT, P->stream));
-  if (x) HIPCHK(hipMemcpyAsync(x, dx, 3 * nf * 8, hipMemcpyDeviceToHost, P->stream));
-  if (v) HIPCHK(hipMemcpyAsync(v, dv, 3 * nf * 8, hipMemcpyDeviceToHost, P->stream));
-  if (rho) HIPCHK(hipMemcpyAsync(rho, dr, nf * 8, hipMemcpyDeviceToHost, P->stream));
-  if (T) HIPCHK(hipMemcpyAsync(T, dT, nf * 8, hipMemcpyDeviceToHost, P->stream));
-  HIPCHK(hipStreamSynchronize(P->stream));
+  hipError_t e =
+      launch_export(P->prec, P->d_table, (int)(&S - P->slots), S.plan.nblk[DOM_FLUID], dx, dv, dr, dT, P->stream);
+  auto out = [&](double* dst, const double* src, size_t n) {
+    if (dst && e == hipSuccess) e = hipMemcpyAsync(dst, src, n * 8, hipMemcpyDeviceToHost, P->stream);
+  };
+  out(x, dx, 3 * nf);
+  out(v, dv, 3 * nf);
+  out(rho, dr, nf);
+  out(T, dT, nf);
+  // also after an error: copies already enqueued write the caller's arrays
+  const hipError_t w = hipStreamSynchronize(P->stream);
+  HIPCHK(e);
+  HIPCHK(w);
   return SPH_OK;
 }
 
