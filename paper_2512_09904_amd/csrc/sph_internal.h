@@ -13,6 +13,7 @@ constexpr int WAVE = 64;            // CDNA wavefront; also the SELL slice heigh
 constexpr int MAX_SLOTS = 32;
 constexpr int NB = SPH_MAX_BODIES;
 constexpr int NACC = 2;             // distinct bodies one fluid particle may touch
+constexpr unsigned CUS = 256;       // compute units of the card
 constexpr int NGLOB = 5;            // mass, kinetic, thermal, mass proxy, vmax
 
 enum Dom { DOM_FLUID = 0, DOM_SOLID = 1, DOM_CELL = 2, DOM_SLOT = 3, NDOM = 4 };
@@ -22,6 +23,7 @@ enum Flag { F_DOMAIN = 1, F_NONFINITE = 2, F_CAPACITY = 4 };
 // their block counts.  Passed by value (kernel argument segment).
 constexpr int32_t TAB_DISS = 1;   // some slot of the launch has viscous heating on
 constexpr int32_t TAB_MAT = 2;    // some slot of the launch has several fluid materials
+constexpr int32_t TAB_STAGE = 4;  // the blocks' candidates are numbered and staged (BlkHead)
 constexpr int NMAT = SPH_MAX_MATERIALS;
 
 struct LaunchTab {
@@ -40,7 +42,8 @@ struct LaunchTab {
 // more candidates than fit (one in ten): three of its wavefronts are staged, the
 // rows of the other hold sorted indices and its lanes gather from memory.  If
 // that does not fit either (one block in a thousand), all four gather.
-// FP64 mode has neither heads nor lists: its rows always hold sorted indices.
+// Without TAB_STAGE, and in FP64 mode, which has neither heads nor lists, all
+// rows hold sorted indices.
 constexpr int STAGE_CAP = 2432;      // 32 B per candidate: two blocks' worth fit the CU's 160 KB
 struct BlkHead {
   int32_t n;                         // candidates (0: none staged)

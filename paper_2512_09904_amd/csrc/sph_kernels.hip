@@ -27,6 +27,11 @@
 // instructions; two blocks fit a CU, and they overlap the two in part.
 // A block in ten has too many candidates for half a CU's LDS; three of its
 // wavefronts are staged then and the fourth gathers.
+//
+// STAGE = false (FP64 mode; launches without TAB_STAGE): nothing is numbered or
+// staged, every row holds sorted indices, and without the staged records' LDS
+// three to five waves per SIMD hide the gathers.  The pairs, their order and their
+// arithmetic are the same, so both give the same bits.
 #include <math.h>
 
 #include <type_traits>
@@ -35,7 +40,7 @@
 
 namespace sphk {
 
-// Gathered rows (FP64 mode, and the wavefronts whose candidates do not fit) are
+// Gathered rows (STAGE = false, and the wavefronts whose candidates do not fit) are
 // walked ROW_UNROLL entries at a time (SOLID_UNROLL for the wall rows,
 // VISC_SOLID_UNROLL for the viscous/heat sweep's wall rows, CONT_UNROLL in the
 // continuity sweep of the staged modes, where a block waits for its gathering
@@ -542,8 +547,8 @@ __global__ __launch_bounds__(BLOCK) void k_reorder(const SlotDesc* table, Launch
 // stores its cell-relative position, from which the sweeps form r_ij.
 //
 // Bound by the candidate loop's instructions: 1.9 M particles take 1014 us with
-// the vector units 72 % busy at five waves per SIMD; numbering the candidates is
-// 70 us of it (939 without).
+// the vector units 72 % busy at five waves per SIMD; numbering the candidates
+// (STAGE) is 70 us of it.
 //
 // A wavefront holds 64 consecutive particles of the Morton order, i.e. runs
 // of particles sharing a cell.  For each run the candidates of its 27-cell
@@ -602,8 +607,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 // first index; lcl (LOCAL): the row entry of its first particle.  Hits of
 // particle p go to its row, counted in lane p's cnt: sorted indices, or (LOCAL)
 // entries of staged rows; own: this lane's particle as such an entry.
-// candidate slots per lane: four keeps the build at five waves per SIMD
-// (92 registers); eight (124 registers, four waves) was 3 % slower
+// candidate slots per lane: four keeps the build at five waves per SIMD (82
+// registers with the numbering, 78 and six waves without); eight (four waves) was
+// 3 % slower
 constexpr int CB = 4;
 template <bool LOCAL, class Pos, class Pos4>
 __device__ __forceinline__ void run_candidates(const GLB Pos4* x, const uint32_t* pre, const uint32_t* beg,
@@ -666,13 +672,15 @@ __device__ __forceinline__ void run_candidates(const GLB Pos4* x, const uint32_t
 // run whose stencil holds its cell (a few tens of runs, 16 on the lattice).
 constexpr int MAXRUN = 64;
 constexpr uint16_t NO_ITEM = 0xffffu, ITEM_REF = 0x8000u;   // no particles; covered by entry (value & 0x7fff)
-constexpr unsigned CUS = 256;          // compute units of the card
 constexpr int WIDE = 4 * BLOCK;  // threads per block of the widest build
-struct StageTab {
+struct RunTab {
+  uint32_t runs[BLOCK / WAVE];
+};
+struct StageTab : RunTab {
   uint32_t home[MAXRUN];
   uint16_t id[2][27 * MAXRUN];       // the entry's item: fluid, solid
   BlkItem item[2][STAGE_ITEMS];
-  uint32_t scan[WIDE / WAVE], last[BLOCK / WAVE], runs[BLOCK / WAVE];
+  uint32_t scan[WIDE / WAVE], last[BLOCK / WAVE];
   int cont1;                         // wavefront 1 starts within a run
 };
 
@@ -758,15 +766,14 @@ __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb
 // NT threads build the rows of BLOCK particles: one thread per particle, each
 // wavefront with its own particles' runs, or (WIDE, WIDE / 2) four or two, so
 // that as many times the wavefronts share the block's runs.
-template <class P, int NT>
+template <class P, int NT, bool STAGE>
 __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab tab) {
 #pragma clang fp contract(off)
   typedef typename P::Pos Pos;
   typedef typename P::Pos4 Pos4;
   typedef typename P::Real4 Real4;
-  constexpr bool CANSTAGE = std::is_same<typename P::Real, float>::value;
   __shared__ uint32_t lr_all[NT / WAVE][6][32];
-  __shared__ StageTab tb;
+  __shared__ typename std::conditional<STAGE, StageTab, RunTab>::type tb;
   // the wavefronts' runs: first particle, cell, run of the block; per particle:
   // row lengths, its own row entry
   __shared__ uint16_t seg_first[BLOCK + 1], seg_run[BLOCK], len[2][BLOCK];
@@ -796,7 +803,7 @@ __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab t
   const uint64_t upto = lane == WAVE - 1 ? ~0ull : (2ull << lane) - 1;
   if (wv < BLOCK / WAVE && lane == WAVE - 1) {
     tb.runs[wv] = (uint32_t)__popcll(runs);
-    tb.last[wv] = pc;
+    if constexpr (STAGE) tb.last[wv] = pc;
   }
   __syncthreads();
   int nseg = 0, seg = __popcll(runs & upto) - 1, seg0 = 0;   // seg0: the wavefront's own first run
@@ -812,7 +819,7 @@ __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab t
   }
   if (threadIdx.x == 0) seg_first[nseg] = (uint16_t)min(BLOCK, nf - lb * BLOCK);
   int waves = 0;   // the particles' wavefronts that are staged
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     // the block's runs, numbered: a wavefront's first one may continue the last one's
     const bool cont = wv > 0 && wv < BLOCK / WAVE && tb.last[max(wv - 1, 0)] == (uint32_t)__builtin_amdgcn_readlane((int)pc, 0);
     const uint64_t heads = cont ? runs & ~1ull : runs;
@@ -837,8 +844,8 @@ __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab t
         if (block_candidates<NT>(S, tb, lb, a == 2 ? cut1 - tb.cont1 : 0, a == 1 ? cut3 : nruns, want)) waves = want;
       }
     }
-    if (waves == 0 && threadIdx.x == 0) S.bhead[lb] = BlkHead{0, 0, 0, 0};
   }
+  if (S.bhead && waves == 0 && threadIdx.x == 0) S.bhead[lb] = BlkHead{0, 0, 0, 0};
   __syncthreads();
   GLB uint32_t* rows = gp<uint32_t>(S.rmaj);
   const GLB uint32_t* rank = gpc<uint32_t>(S.rank);
@@ -853,29 +860,31 @@ __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab t
     const int first = __builtin_amdgcn_readfirstlane((int)seg_first[k]);
     const int R = __builtin_amdgcn_readfirstlane((int)seg_first[k + 1]) - first;
     const uint32_t cell = (uint32_t)__builtin_amdgcn_readfirstlane((int)seg_cell[k]);
-    const bool staged = CANSTAGE && ((waves >> (first / WAVE)) & 1);
+    const bool staged = STAGE && ((waves >> (first / WAVE)) & 1);
     const int wbase = lb * BLOCK + first;
     const int q = wbase + min(lane, R - 1);
     const Pos4 xq = xa[q];
     uint32_t own = (uint32_t)q;
     uint32_t f0 = 0, f1 = 0, s0 = 0, s1 = 0, lf = 0, ls = 0;
     if (staged) {
-      const int e = 27 * __builtin_amdgcn_readfirstlane((int)seg_run[k]);
-      const BlkItem h = tb.item[0][tb.id[0][e + 13]];
-      own = 16u * (h.base + (uint32_t)q - h.start) | 4u * 13u << 16;
-      if (lane < 27) {
-        const uint32_t a = tb.id[0][e + lane], b = tb.id[1][e + lane];
-        if (a != NO_ITEM) {
-          const BlkItem x = tb.item[0][a];
-          f0 = x.start;
-          f1 = f0 + x.cnt;
-          lf = x.base;
-        }
-        if (b != NO_ITEM) {
-          const BlkItem x = tb.item[1][b];
-          s0 = x.start;
-          s1 = s0 + x.cnt;
-          ls = x.base;
+      if constexpr (STAGE) {
+        const int e = 27 * __builtin_amdgcn_readfirstlane((int)seg_run[k]);
+        const BlkItem h = tb.item[0][tb.id[0][e + 13]];
+        own = 16u * (h.base + (uint32_t)q - h.start) | 4u * 13u << 16;
+        if (lane < 27) {
+          const uint32_t a = tb.id[0][e + lane], b = tb.id[1][e + lane];
+          if (a != NO_ITEM) {
+            const BlkItem x = tb.item[0][a];
+            f0 = x.start;
+            f1 = f0 + x.cnt;
+            lf = x.base;
+          }
+          if (b != NO_ITEM) {
+            const BlkItem x = tb.item[1][b];
+            s0 = x.start;
+            s1 = s0 + x.cnt;
+            ls = x.base;
+          }
         }
       }
     } else {
@@ -939,7 +948,7 @@ __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab t
   cf = min(cf, kf);
   cs = min(cs, ks);
   const uint32_t own = own_entry[p];
-  const bool staged = CANSTAGE && ((waves >> (p / WAVE)) & 1);
+  const bool staged = STAGE && ((waves >> (p / WAVE)) & 1);
   constexpr int STEP = 4 * (NT / BLOCK);
   const GLB uint32_t* RM = rows + (int64_t)ip * (kf + ks);
 #pragma unroll
@@ -979,17 +988,16 @@ __global__ __launch_bounds__(NT) void k_build(const SlotDesc* table, LaunchTab t
 // pair's d^2 is formed exactly as in the cutoff test; the rows are walked in
 // order (fluid, then solid) so the sum is reproducible.
 // ---------------------------------------------------------------------------
-template <class P>
+template <class P, bool STAGE>
 __global__ __launch_bounds__(BLOCK) void k_sumw(const SlotDesc* table, LaunchTab tab) {
 #pragma clang fp contract(off)
   typedef typename P::Pos Pos;
   typedef typename P::Real Real;
   typedef typename P::Pos4 Pos4;
   typedef typename P::Real4 Real4;
-  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
   // anchors of the staged candidates (three arrays of coordinates in FP64
   // positions, records in FP32), or the window of the gathering rows
-  constexpr int STAGE_BYTES = CANSTAGE ? STAGE_CAP * (sizeof(Pos) == 8 ? 24 : 16) : 0;
+  constexpr int STAGE_BYTES = STAGE ? STAGE_CAP * (sizeof(Pos) == 8 ? 24 : 16) : 0;
   constexpr int SMEM = STAGE_BYTES > WIN * (int)sizeof(Pos4) ? STAGE_BYTES : WIN * (int)sizeof(Pos4);
   __shared__ __attribute__((aligned(32))) char smem[SMEM];
   SLOT_FIND(DOM_FLUID);
@@ -999,19 +1007,19 @@ __global__ __launch_bounds__(BLOCK) void k_sumw(const SlotDesc* table, LaunchTab
   const GLB Pos4* xw = gpc<Pos4>(S.xw);
   BlkHead hd;
   StageList sl;
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     hd = blk_head(S, lb);
     sl = stage_list(S, lb);
   }
   const Pos4 xi4 = xa[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
   if (!live(S)) return;
-  const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
+  const bool staged = STAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   Pos4* wxa = (Pos4*)smem;
-  const bool block_gathers = !CANSTAGE || hd.n == 0;
+  const bool block_gathers = !STAGE || hd.n == 0;
   const Window win = block_gathers ? window_of(lb, S.nf) : Window{0, 0};
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     if (hd.n > 0) {
       if (staged) {
         ef = row_load(row_groups(S, ii), 0);
@@ -1494,20 +1502,24 @@ __device__ __forceinline__ void grad_add(Real* G, Real c, Real dx, Real dy, Real
 // density, the (T, Drho) record the reorder wrote) instead of the five of
 // the separate launches.
 // ---------------------------------------------------------------------------
-// The staged candidates leave two waves per SIMD: their 256 registers are the
-// budget in FP32 and mixed arithmetic (FP64 keeps the compiler's).
-constexpr int visc_min_waves(bool f64) { return f64 ? 1 : 2; }
-template <class P, bool DISS, bool MAT, bool MOM0>
-__global__ __launch_bounds__(BLOCK)
-    __attribute__((amdgpu_waves_per_eu(visc_min_waves(std::is_same<typename P::Real, double>::value)))) void k_visc_heat(const SlotDesc* table, LaunchTab tab) {
+// The staged candidates leave two waves per SIMD, and their 256 registers are
+// the budget; with heating, 34 to 36 of them spill in mixed arithmetic (108 to 116
+// bytes per lane), 15 to 18 in FP32.  Gathering, the fused sweep without heating
+// is held to three waves in FP32 and mixed arithmetic; the rest is the compiler's.
+constexpr int visc_min_waves(bool stage, bool mom0, bool diss, bool f64) {
+  return stage ? 2 : mom0 && !diss && !f64 ? 3 : 1;
+}
+template <class P, bool DISS, bool MAT, bool MOM0, bool STAGE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(
+    visc_min_waves(STAGE, MOM0, DISS, std::is_same<typename P::Real, double>::value)))) void
+k_visc_heat(const SlotDesc* table, LaunchTab tab) {
   typedef typename P::Real Real;
   typedef typename P::Temp Temp;
   typedef typename P::Real4 Real4;
-  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
   // staged candidates, then (after the rows) the block reductions
   constexpr int RED_BYTES = 4 * NB * (7 + (MOM0 ? 6 : 0)) * 8;
-  __shared__ __attribute__((aligned(32))) char smem[CANSTAGE ? STAGE_CAP * 32 : RED_BYTES];
-  __shared__ float shift[CANSTAGE ? 3 * SHIFT_LD : 1];
+  __shared__ __attribute__((aligned(32))) char smem[STAGE ? STAGE_CAP * 32 : RED_BYTES];
+  __shared__ float shift[STAGE ? 3 * SHIFT_LD : 1];
   double* lds = (double*)smem;
   double* lds_p = lds + 4 * NB * 7;
   __shared__ double lds_d[BLOCK / WAVE];
@@ -1527,7 +1539,7 @@ __global__ __launch_bounds__(BLOCK)
   const GLB Real4* lv = gpc<Real4>(S.lev);
   BlkHead hd;
   StageList sl;
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     hd = blk_head(S, lb);
     sl = stage_list(S, lb);
   }
@@ -1537,7 +1549,7 @@ __global__ __launch_bounds__(BLOCK)
   const Real drhoi = gpc<Real>(S.drho)[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
   if (!live_block(S)) return;
-  const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
+  const bool staged = STAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   const bool mats = MAT && S.mat != nullptr;
   if (mats) {
     for (int q = threadIdx.x; q < NMAT * NMAT; q += BLOCK) {
@@ -1552,7 +1564,7 @@ __global__ __launch_bounds__(BLOCK)
     if (mq == 0) Tb[b] = (Temp)S.bT[b];
   }
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     if (hd.n > 0) {
       if (staged) {
         ef = row_load(row_groups(S, ii), 0);
@@ -1573,7 +1585,7 @@ __global__ __launch_bounds__(BLOCK)
           });
     }
   }
-  if (!CANSTAGE || hd.n == 0) __syncthreads();
+  if (!STAGE || hd.n == 0) __syncthreads();
   const size_t nbf = (size_t)S.nblk[DOM_FLUID];
   if (threadIdx.x < NB * 6) S.press_part[(size_t)threadIdx.x * nbf + lb] = 0.0;
   BodyAcc<7> acc;
@@ -1666,7 +1678,7 @@ __global__ __launch_bounds__(BLOCK)
     };
     wall = nw > 0;
     if (staged) {
-      if constexpr (CANSTAGE) {
+      if constexpr (STAGE) {
         // as staged_row, with the temperature records of a set gathered (at the
         // sorted index in its position record) while the set before is used
         const GLB u4* Gr = row_groups(S, i);
@@ -1923,14 +1935,13 @@ __device__ __forceinline__ void stage_pairs(const SlotDesc& S, const BlkHead& hd
 // half drift x += dt/2 v_new.  Per-block pressure force and torque on each
 // body accumulate over the sub-steps.
 // ---------------------------------------------------------------------------
-template <class P>
+template <class P, bool STAGE>
 __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, LaunchTab tab, int sub) {
   typedef typename P::Real Real;
   typedef typename P::Real4 Real4;
-  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
   // staged candidates, then (after the rows) the block reduction
-  __shared__ __attribute__((aligned(32))) char smem[CANSTAGE ? STAGE_CAP * 32 : 4 * NB * 6 * 8];
-  __shared__ float shift[CANSTAGE ? 3 * SHIFT_LD : 1];
+  __shared__ __attribute__((aligned(32))) char smem[STAGE ? STAGE_CAP * 32 : 4 * NB * 6 * 8];
+  __shared__ float shift[STAGE ? 3 * SHIFT_LD : 1];
   double* lds = (double*)smem;
   SLOT_FIND(DOM_FLUID);
   const int nf = S.nf;
@@ -1941,7 +1952,7 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
   const GLB Real4* lv = gpc<Real4>(S.lev);
   BlkHead hd;
   StageList sl;
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     hd = blk_head(S, lb);
     sl = stage_list(S, lb);
   }
@@ -1949,9 +1960,9 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
   const Real4 oi = xo[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
   if (!live_block(S, sub)) return;
-  const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
+  const bool staged = STAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     if (hd.n > 0) {
       if (staged) {
         ef = row_load(row_groups(S, ii), 0);
@@ -2001,7 +2012,7 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
     };
     wall = nw > 0;
     if (staged) {
-      if constexpr (CANSTAGE) {
+      if constexpr (STAGE) {
         staged_row(row_groups(S, i), ef, nn, smem, shift, oi, pair);
         staged_wall(wall_groups(S, i), ew, nw, smem, shift, [&](const Set4& W, const bool(&real)[4]) {
           const float w[4] = {W.v[0].w, W.v[1].w, W.v[2].w, W.v[3].w};
@@ -2095,13 +2106,12 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
 // the wall's mirror state; writes Drho, commits v <- v_new and applies the
 // half updates that close this sub-step and open the next.
 // ---------------------------------------------------------------------------
-template <class P>
+template <class P, bool STAGE>
 __global__ __launch_bounds__(BLOCK) void k_continuity(const SlotDesc* table, LaunchTab tab, int sub) {
   typedef typename P::Real Real;
   typedef typename P::Real4 Real4;
-  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
-  __shared__ __attribute__((aligned(32))) char smem[CANSTAGE ? STAGE_CAP * 32 : 32];
-  __shared__ float shift[CANSTAGE ? 3 * SHIFT_LD : 1];
+  __shared__ __attribute__((aligned(32))) char smem[STAGE ? STAGE_CAP * 32 : 32];
+  __shared__ float shift[STAGE ? 3 * SHIFT_LD : 1];
   SLOT_FIND(DOM_FLUID);
   const int i = lb * BLOCK + threadIdx.x;
   const int ii = min(i, S.nf - 1);
@@ -2110,7 +2120,7 @@ __global__ __launch_bounds__(BLOCK) void k_continuity(const SlotDesc* table, Lau
   const GLB Real4* nuw = gpc<Real4>(S.nuw);
   BlkHead hd;
   StageList sl;
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     hd = blk_head(S, lb);
     sl = stage_list(S, lb);
   }
@@ -2118,9 +2128,9 @@ __global__ __launch_bounds__(BLOCK) void k_continuity(const SlotDesc* table, Lau
   const Real4 oi = xo[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
   if (!live_sub(S, sub)) return;
-  const bool staged = CANSTAGE && wave_staged(hd, wave_id());   // this wavefront's rows
+  const bool staged = STAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
-  if constexpr (CANSTAGE) {
+  if constexpr (STAGE) {
     if (hd.n > 0) {
       if (staged) {
         ef = row_load(row_groups(S, ii), 0);
@@ -2164,7 +2174,7 @@ __global__ __launch_bounds__(BLOCK) void k_continuity(const SlotDesc* table, Lau
     sum = fma(Vw * (Us - UL) * dot_fma(nq.x, nq.y, nq.z, rx, ry, rz), Fk, sum);
   };
   if (staged) {
-    if constexpr (CANSTAGE) {
+    if constexpr (STAGE) {
       staged_row(row_groups(S, i), ef, nn, smem, shift, oi, pair);
       staged_wall(wall_groups(S, i), ew, nw, smem, shift, [&](const Set4& W, const bool(&real)[4]) {
 #pragma unroll
@@ -2176,7 +2186,7 @@ __global__ __launch_bounds__(BLOCK) void k_continuity(const SlotDesc* table, Lau
       });
       }
   } else {
-    constexpr int U = CANSTAGE ? CONT_UNROLL : ROW_UNROLL;
+    constexpr int U = std::is_same<Real, float>::value ? CONT_UNROLL : ROW_UNROLL;
     const GLB uint32_t* R = gpc<uint32_t>(S.nrec) + slice * (int64_t)S.kf * WAVE + lane;
     uint32_t jn[U];
 #pragma unroll
@@ -2498,7 +2508,7 @@ int grid_domain(int kid, int which) {
   }
 }
 
-template <class P>
+template <class P, bool STAGE>
 static hipError_t launch_p(int kid, int which, int sub, const SlotDesc* T, const LaunchTab& L,
                            hipStream_t st) {
   const int dom = grid_domain(kid, which);
@@ -2524,12 +2534,12 @@ static hipError_t launch_p(int kid, int which, int sub, const SlotDesc* T, const
       // 147 -> 105, but 664 148 -> 153; FP32, 766 blocks: 152 -> 118, FP64 139 ->
       // 123).  Larger grids fill the CUs by themselves, and there the sharing
       // costs a barrier (7437 blocks: 1047 us against 1014).
-      if (g.x <= CUS) hipLaunchKernelGGL((k_build<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
+      if (g.x <= CUS) hipLaunchKernelGGL((k_build<P, WIDE, STAGE>), g, dim3(WIDE), 0, st, T, L);
       else if (g.x <= (sizeof(typename P::Pos) != sizeof(typename P::Real) ? 2 : 3) * CUS)
-        hipLaunchKernelGGL((k_build<P, WIDE / 2>), g, dim3(WIDE / 2), 0, st, T, L);
-      else hipLaunchKernelGGL((k_build<P, BLOCK>), g, b, 0, st, T, L);
+        hipLaunchKernelGGL((k_build<P, WIDE / 2, STAGE>), g, dim3(WIDE / 2), 0, st, T, L);
+      else hipLaunchKernelGGL((k_build<P, BLOCK, STAGE>), g, b, 0, st, T, L);
       break;
-    case SPH_K_SUMW: hipLaunchKernelGGL(k_sumw<P>, g, b, 0, st, T, L); break;
+    case SPH_K_SUMW: hipLaunchKernelGGL((k_sumw<P, STAGE>), g, b, 0, st, T, L); break;
     case SPH_K_CONTACT: hipLaunchKernelGGL(k_contact<P>, g, b, 0, st, T, L, nullptr, nullptr); break;
     case SPH_K_WALLVEL:
       // as the build (92 blocks: 68 -> 28 us, 350: 110 -> 76, 540 in FP32: 89 -> 59); three blocks of 512 threads fit
@@ -2544,23 +2554,23 @@ static hipError_t launch_p(int kid, int which, int sub, const SlotDesc* T, const
       // which = 1: with the first acoustic sub-step's half update and momentum
       if (which == 1) {
         if (L.flags & TAB_MAT) {
-          if (L.flags & TAB_DISS) hipLaunchKernelGGL((k_visc_heat<P, true, true, true>), g, b, 0, st, T, L);
-          else hipLaunchKernelGGL((k_visc_heat<P, false, true, true>), g, b, 0, st, T, L);
+          if (L.flags & TAB_DISS) hipLaunchKernelGGL((k_visc_heat<P, true, true, true, STAGE>), g, b, 0, st, T, L);
+          else hipLaunchKernelGGL((k_visc_heat<P, false, true, true, STAGE>), g, b, 0, st, T, L);
         } else {
-          if (L.flags & TAB_DISS) hipLaunchKernelGGL((k_visc_heat<P, true, false, true>), g, b, 0, st, T, L);
-          else hipLaunchKernelGGL((k_visc_heat<P, false, false, true>), g, b, 0, st, T, L);
+          if (L.flags & TAB_DISS) hipLaunchKernelGGL((k_visc_heat<P, true, false, true, STAGE>), g, b, 0, st, T, L);
+          else hipLaunchKernelGGL((k_visc_heat<P, false, false, true, STAGE>), g, b, 0, st, T, L);
         }
       } else if (L.flags & TAB_MAT) {
-        if (L.flags & TAB_DISS) hipLaunchKernelGGL((k_visc_heat<P, true, true, false>), g, b, 0, st, T, L);
-        else hipLaunchKernelGGL((k_visc_heat<P, false, true, false>), g, b, 0, st, T, L);
+        if (L.flags & TAB_DISS) hipLaunchKernelGGL((k_visc_heat<P, true, true, false, STAGE>), g, b, 0, st, T, L);
+        else hipLaunchKernelGGL((k_visc_heat<P, false, true, false, STAGE>), g, b, 0, st, T, L);
       } else {
-        if (L.flags & TAB_DISS) hipLaunchKernelGGL((k_visc_heat<P, true, false, false>), g, b, 0, st, T, L);
-        else hipLaunchKernelGGL((k_visc_heat<P, false, false, false>), g, b, 0, st, T, L);
+        if (L.flags & TAB_DISS) hipLaunchKernelGGL((k_visc_heat<P, true, false, false, STAGE>), g, b, 0, st, T, L);
+        else hipLaunchKernelGGL((k_visc_heat<P, false, false, false, STAGE>), g, b, 0, st, T, L);
       }
       break;
     case SPH_K_HALF_A: hipLaunchKernelGGL(k_half_a<P>, g, b, 0, st, T, L, sub); break;
-    case SPH_K_MOMENTUM: hipLaunchKernelGGL(k_momentum<P>, g, b, 0, st, T, L, sub); break;
-    case SPH_K_CONTINUITY: hipLaunchKernelGGL(k_continuity<P>, g, b, 0, st, T, L, sub); break;
+    case SPH_K_MOMENTUM: hipLaunchKernelGGL((k_momentum<P, STAGE>), g, b, 0, st, T, L, sub); break;
+    case SPH_K_CONTINUITY: hipLaunchKernelGGL((k_continuity<P, STAGE>), g, b, 0, st, T, L, sub); break;
     case SPH_K_END: hipLaunchKernelGGL(k_end<P>, g, b, 0, st, T, L); break;
     case SPH_K_FINAL: hipLaunchKernelGGL(k_final, g, dim3(FINAL_BLOCK), 0, st, T, L); break;
     default: return hipErrorInvalidValue;
@@ -2627,10 +2637,15 @@ hipError_t launch_contact(int prec, const SlotDesc* table, const LaunchTab& tab,
 
 hipError_t launch_kernel(int prec, int kid, int which, int sub, const SlotDesc* table,
                          const LaunchTab& tab, hipStream_t stream) {
+  const bool stage = tab.flags & TAB_STAGE;
   switch (prec) {
-    case SPH_PREC_MIXED: return launch_p<PMixed>(kid, which, sub, table, tab, stream);
-    case SPH_PREC_FP64: return launch_p<PF64>(kid, which, sub, table, tab, stream);
-    case SPH_PREC_FP32: return launch_p<PF32>(kid, which, sub, table, tab, stream);
+    case SPH_PREC_MIXED:
+      return stage ? launch_p<PMixed, true>(kid, which, sub, table, tab, stream)
+                   : launch_p<PMixed, false>(kid, which, sub, table, tab, stream);
+    case SPH_PREC_FP64: return launch_p<PF64, false>(kid, which, sub, table, tab, stream);
+    case SPH_PREC_FP32:
+      return stage ? launch_p<PF32, true>(kid, which, sub, table, tab, stream)
+                   : launch_p<PF32, false>(kid, which, sub, table, tab, stream);
     default: return hipErrorInvalidValue;
   }
 }

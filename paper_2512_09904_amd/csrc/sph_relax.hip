@@ -193,9 +193,9 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
   __shared__ uint32_t blk_all[BLOCK / WAVE][WAVE];   // active quadrature blocks of a wavefront
   __shared__ double outside[3][QMAX];                // each quadrature block's integral where all of it is outside
   // RQ workgroups per block of BLOCK particles: workgroup `quarter` takes its
-  // WAVE particles, every wavefront forms their neighbour sums and wavefront
-  // w integrates the exterior of the particles with lane % RQ == w (so the
-  // serial per-particle work is spread over RQ times more wavefronts)
+  // WAVE particles, and wavefront w forms the neighbour sums and the exterior
+  // integrals of those with lane % RQ == w (so the serial per-particle work is
+  // spread over RQ times more wavefronts)
   const int vb = xcd_block((int)blockIdx.x, (int)gridDim.x);
   const int quarter = vb % RQ, vblk = vb / RQ;
   int sk = 0;
@@ -228,13 +228,6 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
       outside[2][q] = az;
     }
   }
-  constexpr bool CANSTAGE = std::is_same<Real, float>::value;
-  bool staged = false;
-  const GLB uint32_t* list = nullptr;
-  if constexpr (CANSTAGE) {
-    staged = wave_staged(blk_head(S, lb), quarter);
-    list = gpc<uint32_t>(S.blist) + (int64_t)lb * STAGE_CAP;
-  }
   __syncthreads();
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   const int i = lb * BLOCK + quarter * WAVE + lane;
@@ -257,16 +250,8 @@ __global__ __launch_bounds__(BLOCK) void k_relax_force(const SlotDesc* table, La
     // particle itself, whose pair adds zero
     for (int k = 0; k < n; k += 8) {
       uint32_t j[8];
-      if (staged) {
-        // a staged row's entries name the particles in the block's list
-        uint32_t e[8];
-        row_entries(row_load(row_groups(S, i), k), e);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) j[u] = list[(e[u] & 0xffffu) >> 4];
-      } else {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) j[u] = ldnt(R + (int64_t)(k + u) * WAVE);
-      }
+      for (int u = 0; u < 8; ++u) j[u] = ldnt(R + (int64_t)(k + u) * WAVE);
       Real4 o[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) o[u] = xo[k + u < n ? j[u] : (uint32_t)i];
