@@ -526,9 +526,22 @@ static int enqueue_step(sph_pool* P, const LaunchTab& T, int nac) {
   return SPH_OK;
 }
 
-// FP32 and mixed arithmetic stage the blocks' candidates
+// Whether a launch numbers and stages its blocks' candidates (FP32 and mixed
+// arithmetic).  Narrow kernels have too few neighbours per record (33 at h/dp
+// 1) to win the numbering back; wide ones have more candidates than fit (at 1.75
+// two thirds of the blocks gather all the same, at two waves per SIMD for the
+// staged records' LDS).  A step of 864,000 particles in mixed arithmetic with five
+// acoustic sub-steps (one in brackets), us, gathered and staged: h/dp 1.0 1576 and
+// 1600 (832, 902), 1.1 1837 and 1812 (917, 996), 1.3 3210 and 2737, 1.5 4353 and
+// 3628 (1915, 1825), 1.6 5699 and 5143 (2476, 2435), 1.7 6654 and 6243 (2784,
+// 2837), 1.75 7087 and 7469 (2998, 3351), 2.0 10267 and 11448.  Both give the same
+// bits, so one slot that gains decides for the launch.
 static void tab_stage(sph_pool* P, LaunchTab& T) {
-  if (P->prec != SPH_PREC_FP64) T.flags |= TAB_STAGE;
+  if (P->prec == SPH_PREC_FP64) return;
+  for (int k = 0; k < T.n; ++k) {
+    const double hod = P->slots[T.slot[k]].params.h_over_dp;
+    if (hod >= 1.15 && hod <= 1.72) T.flags |= TAB_STAGE;
+  }
 }
 
 // the launch table of slot `slot` alone (no heap allocation)

@@ -159,3 +159,44 @@ def test_fields_read_back_in_the_callers_order(sph, precision, nf):
     assert np.array_equal(g["v"][fid], st[:, 6:9])
     assert np.array_equal(g["rho"][fid], st[:, 9])
     assert np.array_equal(g["T"][fid], st[:, 11])
+
+
+def _wide(c, hod):
+    """The case with the smoothing length hod dp and rows that hold its neighbours."""
+    p = c.params
+    m = 2.0 * hod * p["dp"] + 3 * p["dp"]
+    p.update(h_over_dp=hod, grid_lo=(-m,) * 3, grid_hi=tuple(float(x) + m for x in c.meta["box"]),
+             max_fluid_nbrs=int(48 * hod ** 3) + 32, max_solid_nbrs=int(32 * hod ** 3) + 48)
+    return c
+
+
+@pytest.mark.parametrize("heated", [False, True])
+@pytest.mark.parametrize("precision", ["mixed", "fp32"])
+@pytest.mark.parametrize("hod", [1.0, 2.0])
+def test_staged_and_gathered_launches_agree(sph, precision, hod, heated):
+    """A solve with a narrow or a wide kernel gathers when it runs alone; beside
+    one whose kernel is between them the launch stages its candidates.  The same
+    bits, with and without dissipation heating and two materials."""
+    a, b = _wide(cases.tank_c1(seed=8), hod), cases.tank_c1(seed=9)
+    if heated:
+        for c in (a, b):
+            c.params.update(viscous_heating=1, materials=[(0.13, 2000.0), (0.45, 1300.0)])
+            c.material = (c.xf[:, 0] > 0.05).astype(np.int32)
+    res = []
+    for reqs in ([a], [b, a]):
+        pool = sph.Pool(1 << 40, max_slots=2, precision=precision)
+        slots = [pool.admit(c, 4) for c in reqs]
+        pool.step(4)
+        done = False
+        while not done:
+            done, rep = pool.poll(slots[-1])
+        assert rep["rc"] == 0
+        res.append((pool.get_fluid(slots[-1]), rep))
+        pool.close()
+    (f0, r0), (f1, r1) = res
+    for k in ("x", "v", "rho", "T"):
+        assert np.array_equal(f0[k], f1[k]), k
+    assert r0["t"] == r1["t"] and r0["kinetic"] == r1["kinetic"] and r0["diss_total"] == r1["diss_total"]
+    for x, y in zip(r0["bodies"], r1["bodies"]):
+        for k in ("force", "torque", "heat_int"):
+            assert np.array_equal(x[k], y[k]), k
