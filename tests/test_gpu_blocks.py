@@ -200,3 +200,73 @@ def test_staged_and_gathered_launches_agree(sph, precision, hod, heated):
     for x, y in zip(r0["bodies"], r1["bodies"]):
         for k in ("force", "torque", "heat_int"):
             assert np.array_equal(x[k], y[k]), k
+
+
+def _in_fp32(c):
+    f32 = lambda a: np.asarray(a, dtype=np.float32).astype(np.float64)
+    c.xf, c.rhof, c.Tf, c.vf = f32(c.xf), f32(c.rhof), f32(c.Tf), f32(c.vf)
+    return c
+
+
+KINDS = [
+    ("wide", lambda k: k >= 0, 1.6, {"whole", "three", "gather"}),
+    ("tank", lambda k: k >= 0, 1.3, {"whole", "three"}),
+    ("ragged", lambda k: (k < BLOCK + 65) & (k % 41 != 0), 1.3, {"whole"}),
+    ("thinned", lambda k: k % 13 == 0, 1.3, {"gather"}),
+    ("isolated", lambda k: k % 997 == 5, 1.3, {"whole"}),
+    ("one", lambda k: k == 4000, 1.3, {"whole"}),
+]
+
+
+@pytest.mark.parametrize("precision,name,keep,hod,want",
+                         [("mixed",) + KINDS[0]] + [("fp32",) + k for k in KINDS])
+def test_rows_of_every_kind_of_block_wide_and_in_fp32(sph, ora, precision, name, keep, hod, want):
+    """As above with blocks that gather because their candidates do not fit (few
+    runs, a wide kernel), and in all-FP32 arithmetic.  Bars: mixed as above; FP32
+    those of one step in that mode (test_gpu_parity): sets up to pairs within 1e-5
+    of the cutoff, x, rho, T within 20 ulps, v within what 20 ulps of the density
+    imply through the pressure."""
+    c = _tank(keep)
+    if hod != 1.3:
+        c = _wide(c, hod)
+    if precision == "fp32":
+        c = _in_fp32(c)
+    kinds = _kinds(ora, c)
+    say("blocks", name, precision, c.nf, {k: kinds.count(k) for k in set(kinds)})
+    assert want <= set(kinds)
+    rc, order = ora.sort_order(c.params, c.xf, np.arange(c.nf, dtype=np.uint32))
+    cf = np.asarray(ora.cells(c.params, c.xf[order])[1])
+    runs = [1 + int(np.sum(np.any(np.diff(cf[b:b + BLOCK], axis=0), axis=1))) for b in range(0, c.nf, BLOCK)]
+    if name == "wide":
+        assert max(runs) <= RUNS   # the candidates decide
+    xs, _, _ = ora.body_pose(c.bodies, c.xs0, c.ns0, c.body, 0.0)
+    nb = ora.Nbr(c.params, c.xf, xs)
+    d = ora.timestep(c.params, c.bodies, c.xs0, c.body, c.vf)
+    dt, nac = d["dt_ad"], d["n_ac"]
+    o = ora.State(c, fixed_dt_ad=dt, fixed_nac=nac)
+    ro = o.step()
+    s = sph.Solver(c, precision=precision, fixed_dt_ad=dt, fixed_nac=nac)
+    fl, so = s.neighbour_sets()
+    cut2 = (2.0 * c.params["h_over_dp"] * c.params["dp"]) ** 2
+    for got, ref, x in ((fl, nb.sets(0), c.xf), (so, nb.sets(1), np.asarray(xs))):
+        for i in range(c.nf):
+            for j in got[i] ^ ref[i]:
+                assert precision == "fp32", (i, j)
+                assert abs(float(np.sum((c.xf[i] - x[j]) ** 2)) - cut2) <= 1e-5 * cut2, (i, j)
+    s.step(1)
+    rg = s.reduce()
+    g = s.get_fluid()
+    s.close()
+    p, umax = c.params, c.meta["umax"]
+    scale = dict(x=p["dp"], v=umax, rho=p["rho0"] * (umax / p["c0"]) ** 2, T=abs(c.bodies[0].T - c.Tf.mean()))
+    bar = {k: 1e-5 * q for k, q in scale.items()}
+    if precision == "fp32":
+        ulp = lambda a: float(np.spacing(np.float32(np.max(np.abs(a)))))
+        drho = 20 * ulp(o.rho)
+        bar = dict(x=20 * ulp(o.x), v=dt * 6.0 * p["c0"] ** 2 * drho / (p["rho0"] * p["h_over_dp"] * p["dp"]),
+                   rho=drho, T=20 * ulp(o.T))
+    e = {k: np.max(np.abs(g[k] - getattr(o, k))) for k in scale}
+    say("errors over bars", {k: e[k] / bar[k] for k in e})
+    for k in e:
+        assert e[k] <= bar[k], (k, e[k], bar[k])
+    assert rg["n_ac"] == ro["n_ac"]
