@@ -67,6 +67,7 @@ struct Plan {
   int32_t ncells = 0, dims[3] = {0, 0, 0}, nslices = 0, kf = 0, ks = 0;
   int32_t nblk[NDOM] = {0, 0, 0, 0};
   int64_t rowlen_f = 0, rowlen_s = 0;
+  int32_t list_len = 0;   // entries of a block's candidate list
   int32_t nmat = 1;
   size_t pos_sz = 8, real_sz = 4, temp_sz = 8;
   size_t total = 0;
@@ -115,6 +116,8 @@ static int make_plan(const sph_params* p, int prec, int64_t nf, int64_t ns, Plan
   P->kf = ((p->max_fluid_nbrs > 0 ? p->max_fluid_nbrs : 128) + 15) & ~15;
   P->ks = ((p->max_solid_nbrs > 0 ? p->max_solid_nbrs : 96) + 15) & ~15;
   if (P->kf > 1024 || P->ks > 1024) return fail(SPH_ERR_ARG, "neighbour capacity above 1024");
+  // no more candidates than particles (the solids start at a multiple of WAVE)
+  P->list_len = (int32_t)std::min<int64_t>(STAGE_CAP, ceil_div(nf, WAVE) * WAVE + ns);
   P->nslices = (int32_t)ceil_div(nf, WAVE);
   P->rowlen_f = (int64_t)P->nslices * P->kf * WAVE;
   P->rowlen_s = (int64_t)P->nslices * P->ks * WAVE;
@@ -167,25 +170,29 @@ static size_t carve(const Plan& P, void* base, SlotDesc* d) {
   C.take(D.fcell, nf * 4);
   C.take(D.fperm, nf * 4);
   C.take(D.fkey, nf * 8);
-  C.takev(D.xa2, 4 * nf * ps);
-  C.takev(D.vr2, 4 * nf * rs);
-  C.takev(D.drho2, nf * rs);
-  C.takev(D.T2, nf * ts);
-  C.take(D.fid2, nf * 4);
-  if (P.nmat > 1) {
-    C.take(D.mat, nf * 4);
-    C.take(D.mat2, nf * 4);
-  }
+  if (P.nmat > 1) C.take(D.mat, nf * 4);
   C.take(D.nfc, nf * 4);
   C.take(D.nsc, nf * 4);
   C.take(D.nrec, 4 * (size_t)P.rowlen_f);
   C.take(D.srec, 4 * (size_t)P.rowlen_s);
   if (P.prec != SPH_PREC_FP64) {   // what the staged sweeps read
     C.take(D.bhead, nbf * sizeof(BlkHead));
-    C.take(D.blist, nbf * STAGE_CAP * 4);
-    C.takev(D.vdb, 4 * ns * rs);
+    C.take(D.blist, nbf * (size_t)P.list_len * 4);
   }
+  // the fluid's gather buffers (from the fold to the reorder) and the build's
+  // scratch rows (during the build) in the same memory
+  C.off = (C.off + 255) & ~(size_t)255;
+  const size_t shared = C.off;
+  C.takev(D.xa2, 4 * nf * ps);
+  C.takev(D.vr2, 4 * nf * rs);
+  C.takev(D.drho2, nf * rs);
+  C.takev(D.T2, nf * (ts + 4));
+  D.fid2 = base ? (uint32_t*)((char*)D.T2 + nf * ts) : nullptr;
+  if (P.nmat > 1) C.take(D.mat2, nf * 4);
+  const size_t gather_end = C.off;
+  C.off = shared;
   C.take(D.rmaj, 4 * nf * (size_t)(P.kf + P.ks));
+  C.off = std::max(C.off, gather_end);
   C.takev(D.xo, 4 * nf * rs);
   C.takev(D.so, 4 * ns * rs);
   C.takev(D.x0, ns * 32);
@@ -193,10 +200,10 @@ static size_t carve(const Plan& P, void* base, SlotDesc* d) {
   C.take(D.body, ns * 4);
   C.take(D.sid, ns * 4);
   C.takev(D.xw, 4 * ns * ps);
-  C.takev(D.nw, 4 * ns * rs);
   C.takev(D.vw, 4 * ns * rs);
   C.takev(D.lev, 4 * ns * rs);
   C.takev(D.x0b, ns * 32);
+  D.zeta = (double*)D.x0b;   // written and read back after a reorder has emptied the buffer
   C.takev(D.n0b, ns * 32);
   C.take(D.bodyb, ns * 4);
   C.take(D.sidb, ns * 4);
@@ -206,7 +213,6 @@ static size_t carve(const Plan& P, void* base, SlotDesc* d) {
   C.takev(D.levb, 4 * ns * rs);
   C.take(D.scell, ns * 4);
   C.take(D.sperm, ns * 4);
-  C.take(D.zeta, ns * 8);
   C.takev(D.vd, 4 * ns * rs);
   C.takev(D.nuw, 4 * ns * rs);
   C.take(D.skey, ns * 8);
@@ -763,6 +769,7 @@ static int admit(sph_pool* P, const sph_params* p, int32_t nbody, const sph_body
   D.ns = (int32_t)ns;
   D.ncells = pl.ncells;
   D.nslices = pl.nslices;
+  D.list_len = pl.list_len;
   D.kf = pl.kf;
   D.ks = pl.ks;
   D.nbody = nbody;
@@ -1446,14 +1453,14 @@ extern "C" int sph_debug_dump(sph_solver* s, int32_t what, void* buf, size_t byt
       // in groups of four entries; back to sorted indices by the block's list
       const size_t nb = (size_t)pl.nblk[DOM_FLUID];
       std::vector<BlkHead> hd(nb);
-      std::vector<uint32_t> list(nb * STAGE_CAP), cnt(nf);
+      std::vector<uint32_t> list(nb * (size_t)pl.list_len), cnt(nf);
       LCHK(d2h(hd.data(), D.bhead, nb * sizeof(BlkHead)));
       LCHK(d2h(list.data(), D.blist, list.size() * 4));
       LCHK(d2h(cnt.data(), sol ? D.nsc : D.nfc, nf * 4));
       for (size_t i = 0; i < nf; ++i) {
         if (!(hd[i / BLOCK].waves >> (i % BLOCK / WAVE) & 1)) continue;
         const uint32_t* row = r.data() + (i / WAVE) * (size_t)K * WAVE;
-        const uint32_t* glob = list.data() + (i / BLOCK) * STAGE_CAP;
+        const uint32_t* glob = list.data() + (i / BLOCK) * (size_t)pl.list_len;
         for (size_t k = 0; k < (size_t)K; ++k)
           o[i * (size_t)K + k] =
               k < cnt[i] ? glob[(row[((k / 4) * WAVE + i % WAVE) * 4 + k % 4] & 0xffffu) / 16] : 0u;
@@ -1511,7 +1518,7 @@ extern "C" int sph_debug_dump(sph_solver* s, int32_t what, void* buf, size_t byt
       std::vector<char> x(4 * ns * ps), n(4 * ns * rs), v(4 * ns * rs), l(4 * ns * rs);
       std::vector<int32_t> b(ns);
       LCHK(d2h(x.data(), D.xw, x.size()));
-      LCHK(d2h(n.data(), D.nw, n.size()));
+      LCHK(d2h(n.data(), D.nuw, n.size()));
       LCHK(d2h(v.data(), D.vw, v.size()));
       LCHK(d2h(l.data(), D.lev, l.size()));
       LCHK(d2h(b.data(), D.body, ns * 4));
@@ -1530,10 +1537,12 @@ extern "C" int sph_debug_dump(sph_solver* s, int32_t what, void* buf, size_t byt
     }
     case SPH_DUMP_SUMW: return d2h(buf, D.sumW, nf * 8);
     case SPH_DUMP_SOLID_DUMMY: {
-      std::vector<char> r(4 * ns * rs);
+      // the velocity, and its kernel sum beside the rigid velocity
+      std::vector<char> r(4 * ns * rs), v(4 * ns * rs);
       LCHK(d2h(r.data(), D.vd, r.size()));
+      LCHK(d2h(v.data(), D.vw, v.size()));
       double* o = (double*)buf;
-      for (size_t k = 0; k < 4 * ns; ++k) o[k] = get_as_double(r.data(), k, rs);
+      for (size_t k = 0; k < 4 * ns; ++k) o[k] = get_as_double(k % 4 == 3 ? v.data() : r.data(), k, rs);
       return SPH_OK;
     }
     default: return fail(SPH_ERR_ARG, "unknown dump selector");

@@ -375,10 +375,11 @@ struct StageList {
   uint32_t j[STAGE_U];
 };
 __device__ __forceinline__ StageList stage_list(const SlotDesc& S, int lb) {
-  const GLB uint32_t* list = gpc<uint32_t>(S.blist) + (int64_t)lb * STAGE_CAP;
+  const int len = S.list_len;
+  const GLB uint32_t* list = gpc<uint32_t>(S.blist) + (int64_t)lb * len;
   StageList s;
 #pragma unroll
-  for (int u = 0; u < STAGE_U; ++u) s.j[u] = list[min(u * BLOCK + (int)threadIdx.x, STAGE_CAP - 1)];
+  for (int u = 0; u < STAGE_U; ++u) s.j[u] = list[min(u * BLOCK + (int)threadIdx.x, len - 1)];
   return s;
 }
 

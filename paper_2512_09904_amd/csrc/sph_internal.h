@@ -90,6 +90,7 @@ struct SlotCtl {
 struct SlotDesc {
   int32_t nf, ns, ncells, nslices;
   int32_t kf, ks, nbody, nac_bound;
+  int32_t list_len;                    // entries of a block's candidate list: STAGE_CAP, or all particles
   int32_t dims[3];
   int32_t free_surface, fixed_nac, diss;   // diss: viscous dissipation heating on
   int32_t nblk[NDOM];
@@ -121,23 +122,22 @@ struct SlotDesc {
   uint32_t *nfc, *nsc;
   uint32_t *nrec, *srec;
   BlkHead *bhead;       // per fluid block
-  uint32_t *blist;      // [fluid block][STAGE_CAP]: the candidates' sorted indices
-  uint32_t *rmaj;       // build output: per particle kf fluid then ks solid entries
+  uint32_t *blist;      // [fluid block][list_len]: the candidates' sorted indices
+  uint32_t *rmaj;       // build output: per particle kf fluid then ks solid entries (in the gather buffers' memory)
   void *xo, *so;
   // solids: FP64 reference pose (x, y, z, 0) and normal, body; current pose
   void *x0, *n0;
   int32_t *body;
   uint32_t *sid;
-  void *xw, *nw, *vw, *lev;
+  void *xw, *vw, *lev;  // vw: rigid velocity and dp^3 sum W of the dummy velocity
   void *x0b, *n0b;
   int32_t *bodyb;
   uint32_t *sidb;
   void *xwb, *nwb, *vwb, *levb;
   uint32_t *scell, *sperm;
-  double *zeta;         // contact factor per solid particle, original order
-  void *nuw;            // wall normal and u_w = -n . v_w per sorted solid particle (FP32 sweeps)
-  void *vdb;            // dummy velocity and body per sorted solid particle (FP32 sweeps)
-  void *vd;             // dummy velocity of eq. 18 per sorted solid particle (vx, vy, vz, dp^3 sum W)
+  double *zeta;         // contact factor per solid particle, original order (in x0b)
+  void *nuw;            // wall normal and u_w = -n . v_w per sorted solid particle
+  void *vd;             // dummy velocity of eq. 18 and body per sorted solid particle
   uint64_t *skey;
   // cells
   uint32_t *rank, *cnt_f, *cnt_s, *start_f, *start_s, *bsum_f, *bsum_s;

@@ -530,7 +530,6 @@ __global__ __launch_bounds__(BLOCK) void k_reorder(const SlotDesc* table, Launch
     gp<Real4>(S.so)[k] = cell_offset<P>(S, xp.x, xp.y, xp.z, c);
     Real4 nq = gpc<Real4>(S.nwb)[s];
     const Real4 vq = gpc<Real4>(S.vwb)[s];
-    gp<Real4>(S.nw)[k] = nq;
     gp<Real4>(S.vw)[k] = vq;
     nq.w = -dot_fma(nq.x, nq.y, nq.z, vq.x, vq.y, vq.z);
     gp<Real4>(S.nuw)[k] = nq;
@@ -742,7 +741,7 @@ __device__ __forceinline__ bool block_candidates(const SlotDesc& S, StageTab& tb
   const bool ok = !__syncthreads_or(big) && nt <= STAGE_CAP && ni[0] < STAGE_ITEMS && ni[1] < STAGE_ITEMS;
   if (!ok) return false;
   if (threadIdx.x == 0) S.bhead[lb] = BlkHead{nt, ns0, waves, 0};
-  uint32_t* list = S.blist + (int64_t)lb * STAGE_CAP;
+  uint32_t* list = S.blist + (int64_t)lb * S.list_len;
   if (nc[0] + (int)threadIdx.x < ns0) list[nc[0] + threadIdx.x] = 0u;
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
@@ -1316,11 +1315,9 @@ __global__ __launch_bounds__(NT) void k_wallvel(const SlotDesc* table, LaunchTab
     o.z = (Real)(2.0 * (double)u.z - (double)acc[2] * inv);
     o.w = (Real)((double)acc[3] * (S.dp * S.dp * S.dp));
   }
+  gp<Real>(S.vw)[4 * (int64_t)w + 3] = o.w;
+  o.w = gpc<Real4>(S.lev)[w].w;   // the body, which the staged record names
   gp<Real4>(S.vd)[w] = o;
-  if constexpr (std::is_same<Real, float>::value) {   // the staged sweeps' record
-    o.w = gpc<Real4>(S.lev)[w].w;   // the body
-    gp<Real4>(S.vdb)[w] = o;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1572,11 +1569,10 @@ k_visc_heat(const SlotDesc* table, LaunchTab tab) {
       }
       shift_table(shift, (float)S.cs_r);
       const GLB f4* so = gpc<f4>(S.so);
-      const GLB f4* vdb = gpc<f4>(S.vdb);
       // the position record's fourth word takes the sorted index, at which the
       // temperature record or the lever arm is gathered
       stage_block(
-          hd, sl, [&](bool sol, uint32_t j) { return RecPair{(sol ? so : xo)[j], (sol ? vdb : vr)[j]}; },
+          hd, sl, [&](bool sol, uint32_t j) { return RecPair{(sol ? so : xo)[j], (sol ? vdw : vr)[j]}; },
           [&](uint32_t l, const RecPair& r, uint32_t j) {
             f4 o = r.a;
             o.w = pack_index(j, 0.0f);

@@ -68,3 +68,26 @@ def test_an_allocator_is_required_without_gpu():
     assert not h.value
     assert L.sph_pool_create(ctypes.c_size_t(1 << 30), 4, 0, None, None, ctypes.byref(h)) == sph.SPH_ERR_ARG
     assert not h.value
+
+
+# sph_bytes_required of a tank before the sweeps staged their neighbours: a budget
+# that held a solve then still holds it
+BYTES = {
+    ("mixed", 1, 0, 0): 162048, ("mixed", 1, 0, 16): 112128, ("mixed", 100, 50, 0): 351488,
+    ("mixed", 257, 0, 16): 239872, ("mixed", 769, 0, 0): 1724928, ("mixed", 12240, 23456, 0): 33501184,
+    ("mixed", 12240, 23456, 16): 14663680, ("mixed", 50000, 0, 16): 25079296, ("mixed", 888440, 478448, 0): 1980740096,
+    ("fp32", 1, 0, 16): 112128, ("fp32", 10, 0, 0): 169984, ("fp32", 257, 0, 0): 672768,
+    ("fp32", 769, 0, 16): 464640, ("fp32", 12240, 23456, 16): 13423616, ("fp32", 50000, 0, 0): 99916288,
+    ("fp32", 888440, 478448, 16): 565242368,
+    ("fp64", 1, 0, 16): 112128, ("fp64", 100, 50, 16): 192768, ("fp64", 12240, 23456, 0): 37776384,
+    ("fp64", 888440, 478448, 0): 2134378496,
+}
+
+
+@pytest.mark.parametrize("precision,nf,ns,caps", list(BYTES))
+def test_a_solve_takes_no_more_memory_than_before(precision, nf, ns, caps):
+    from paper_2512_09904_amd import cases, sph
+    c = cases.tank_c1()
+    P = sph.params_struct(c.params, precision, max_fluid_nbrs=caps, max_solid_nbrs=caps)
+    got = sph.lib().sph_bytes_required(ctypes.byref(P), nf, ns)
+    assert 0 < got <= BYTES[precision, nf, ns, caps]
