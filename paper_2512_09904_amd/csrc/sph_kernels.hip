@@ -2538,12 +2538,21 @@ static hipError_t launch_p(int kid, int which, int sub, const SlotDesc* T, const
     case SPH_K_SUMW: hipLaunchKernelGGL((k_sumw<P, STAGE>), g, b, 0, st, T, L); break;
     case SPH_K_CONTACT: hipLaunchKernelGGL(k_contact<P>, g, b, 0, st, T, L, nullptr, nullptr); break;
     case SPH_K_WALLVEL:
-      // as the build (92 blocks: 68 -> 28 us, 350: 110 -> 76, 540 in FP32: 89 -> 59); three blocks of 512 threads fit
-      // a CU in FP32 and mixed arithmetic, one in FP64
-      if (g.x <= CUS) hipLaunchKernelGGL((k_wallvel<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
-      else if (sizeof(typename P::Real) == 4 && g.x <= 3 * CUS)
-        hipLaunchKernelGGL((k_wallvel<P, WIDE / 2>), g, dim3(WIDE / 2), 0, st, T, L);
-      else hipLaunchKernelGGL((k_wallvel<P, BLOCK>), g, b, 0, st, T, L);
+      // as the build (mixed: 92 blocks 68 -> 28 us, 350 110 -> 76; FP32: 540 89 -> 59;
+      // FP64, which spills 20 bytes per lane at 1024 threads: 92 99 -> 49, 214 114 ->
+      // 80); three blocks of 512 threads fit a CU in FP32 and mixed arithmetic, one in
+      // FP64, which keeps blocks of 256 beyond 256 blocks
+      if (g.x <= CUS) {
+        hipLaunchKernelGGL((k_wallvel<P, WIDE>), g, dim3(WIDE), 0, st, T, L);
+        break;
+      }
+      if constexpr (sizeof(typename P::Real) == 4) {
+        if (g.x <= 3 * CUS) {
+          hipLaunchKernelGGL((k_wallvel<P, WIDE / 2>), g, dim3(WIDE / 2), 0, st, T, L);
+          break;
+        }
+      }
+      hipLaunchKernelGGL((k_wallvel<P, BLOCK>), g, b, 0, st, T, L);
       break;
     case SPH_K_DT: hipLaunchKernelGGL(k_dt, g, b, 0, st, T, L); break;
     case SPH_K_VISC_HEAT:
