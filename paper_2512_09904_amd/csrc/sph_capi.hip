@@ -535,8 +535,8 @@ static int enqueue_step(sph_pool* P, const LaunchTab& T, int nac) {
 // Whether a launch numbers and stages its blocks' candidates (FP32 and mixed
 // arithmetic).  Narrow kernels have too few neighbours per record (33 at h/dp
 // 1) to win the numbering back; wide ones have more candidates than fit (at 1.75
-// two thirds of the blocks gather all the same, at two waves per SIMD for the
-// staged records' LDS).  A step of 864,000 particles in mixed arithmetic with five
+// about half of the blocks gather whole all the same, at two waves per SIMD for
+// the staged records' LDS).  A step of 864,000 particles in mixed arithmetic with five
 // acoustic sub-steps (one in brackets), us, gathered and staged: h/dp 1.0 1576 and
 // 1600 (832, 902), 1.1 1837 and 1812 (917, 996), 1.3 3210 and 2737, 1.5 4353 and
 // 3628 (1915, 1825), 1.6 5699 and 5143 (2476, 2435), 1.7 6654 and 6243 (2784,

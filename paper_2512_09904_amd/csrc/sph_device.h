@@ -92,15 +92,15 @@ __device__ __forceinline__ bool live_sub(const SlotDesc& S, int sub) {
   return live(S) & (sub < n_ac);
 }
 
-// The same, decided once for the whole workgroup (thread 0's reading; sub < 0:
-// live), with a barrier.  For the kernels that raise flags and whose wavefronts
-// take indices from each other through LDS: another workgroup may raise a flag
-// between two wavefronts' own readings, and the wavefronts that stayed would
-// follow indices that the others never wrote.  Elsewhere a launch either raises
-// no flags or shares no more than sums, which nobody reads of a faulted solve.
-__device__ __forceinline__ bool live_block(const SlotDesc& S, int sub = -1) {
+// The same, decided once for the whole workgroup (thread 0's reading), with a
+// barrier.  For the kernels that raise flags and whose wavefronts take indices
+// from each other through LDS: another workgroup may raise a flag between two
+// wavefronts' own readings, and the wavefronts that stayed would follow indices
+// that the others never wrote.  Elsewhere a launch either raises no flags or
+// shares no more than sums, which nobody reads of a faulted solve.
+__device__ __forceinline__ bool live_block(const SlotDesc& S) {
   __shared__ int go;
-  if (threadIdx.x == 0) go = sub < 0 ? live(S) : live_sub(S, sub);
+  if (threadIdx.x == 0) go = live(S);
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(go) != 0;
 }

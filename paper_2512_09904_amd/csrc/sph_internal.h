@@ -39,9 +39,9 @@ struct LaunchTab {
 // candidates' records in LDS and the block's rows hold
 //   16 * (local index) | 4 * (stencil cell 0..26) << 16
 // in groups of four.  A block that straddles a jump of the Morton order has
-// more candidates than fit (one in ten): three of its wavefronts are staged, the
-// rows of the other hold sorted indices and its lanes gather from memory.  If
-// that does not fit either (one block in a thousand), all four gather.
+// more candidates than fit (one in ten at h/dp 1.3): three of its wavefronts are
+// staged, the rows of the other hold sorted indices and its lanes gather from
+// memory.  If that does not fit either (one block in a thousand), all four gather.
 // Without TAB_STAGE, and in FP64 mode, which has neither heads nor lists, all
 // rows hold sorted indices.
 constexpr int STAGE_CAP = 2432;      // 32 B per candidate: two blocks' worth fit the CU's 160 KB

@@ -1940,6 +1940,9 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
   __shared__ float shift[STAGE ? 3 * SHIFT_LD : 1];
   double* lds = (double*)smem;
   SLOT_FIND(DOM_FLUID);
+  // launches past the step's sub-steps leave before the loads and the barrier (6 us
+  // each with them); no launch that reads n_ac writes it
+  if (sub >= gpc<SlotCtl>(S.ctl)->n_ac) return;
   const int nf = S.nf;
   const int i = lb * BLOCK + threadIdx.x;
   const int ii = min(i, nf - 1);
@@ -1955,7 +1958,7 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(const SlotDesc* table, Launc
   const Real4 vi = vr[ii];
   const Real4 oi = xo[ii];
   const int nn = (int)S.nfc[ii], nw = (int)S.nsc[ii];
-  if (!live_block(S, sub)) return;
+  if (!live_block(S)) return;
   const bool staged = STAGE && wave_staged(hd, wave_id());   // this wavefront's rows
   Row8 ef{u4(0), u4(0)}, ew{u4(0), u4(0)};
   if constexpr (STAGE) {
