@@ -530,7 +530,10 @@ __global__ __launch_bounds__(BLOCK) void k_reorder(const SlotDesc* table, Launch
     gp<Real4>(S.so)[k] = cell_offset<P>(S, xp.x, xp.y, xp.z, c);
     Real4 nq = gpc<Real4>(S.nwb)[s];
     const Real4 vq = gpc<Real4>(S.vwb)[s];
-    gp<Real4>(S.vw)[k] = vq;
+    GLB Real* vk = gp<Real>(S.vw) + 4 * (int64_t)k;   // not the kernel sum beside it
+    vk[0] = vq.x;
+    vk[1] = vq.y;
+    vk[2] = vq.z;
     nq.w = -dot_fma(nq.x, nq.y, nq.z, vq.x, vq.y, vq.z);
     gp<Real4>(S.nuw)[k] = nq;
     gp<Real4>(S.lev)[k] = gpc<Real4>(S.levb)[s];

@@ -270,3 +270,22 @@ def test_rows_of_every_kind_of_block_wide_and_in_fp32(sph, ora, precision, name,
     for k in e:
         assert e[k] <= bar[k], (k, e[k], bar[k])
     assert rg["n_ac"] == ro["n_ac"]
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp32", "fp64"])
+def test_dummy_velocities_outlast_a_contact_reading(sph, precision):
+    """The contact factor's sort and build leave the last step's dummy velocities
+    and their kernel sums as they are (the walls at rest keep their places)."""
+    c = cases.tank_c1(seed=4)
+    s = sph.Solver(c, precision=precision)
+    s.step(2)
+    s.reduce()
+    sid = s.dump("solid_ids").copy()
+    d0 = s.dump("solid_dummy").reshape(c.ns, 4).copy()
+    assert (d0[:, 3] > 0).any()
+    s.contact_factor()
+    still = (s.dump("solid_ids") == sid) & (c.body[sid] == 0)
+    assert still.any()
+    d1 = s.dump("solid_dummy").reshape(c.ns, 4)
+    s.close()
+    assert np.array_equal(d0[still], d1[still])
